@@ -121,10 +121,30 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
   v += swap16_u64(v);           // each 32-lane half holds its sum
   return readlane_u64(v, 0) + readlane_u64(v, 32);
 }
+// maximum over each row of 16 lanes, in every lane of the row
+__device__ __forceinline__ float row_max(float v) {
+  v = fmaxf(v, RBQ_DPP(v, 0xB1));
+  v = fmaxf(v, RBQ_DPP(v, 0x4E));
+  v = fmaxf(v, RBQ_DPP(v, 0x141));
+  return fmaxf(v, RBQ_DPP(v, 0x140));
+}
 __device__ __forceinline__ float wave_max_dpp(float v) {
   v = max32(v);
   return fmaxf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0)),
                __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32)));
+}
+__device__ __forceinline__ int wave_max_i32(int v) {
+#define RBQ_DPP_I32(v, ctrl) __builtin_amdgcn_update_dpp(0, (v), (ctrl), 0xF, 0xF, false)
+  v = max(v, RBQ_DPP_I32(v, 0xB1));
+  v = max(v, RBQ_DPP_I32(v, 0x4E));
+  v = max(v, RBQ_DPP_I32(v, 0x141));
+  v = max(v, RBQ_DPP_I32(v, 0x140));
+  v = max(v, __builtin_amdgcn_ds_swizzle(v, 0x401F));
+#undef RBQ_DPP_I32
+  return max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 32));
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  return uint32_t(wave_max_i32(int(v ^ 0x80000000u))) ^ 0x80000000u;
 }
 __device__ __forceinline__ int wave_sum_i32(int v) {
   v += int(RBQ_DPP_U32(uint32_t(v), 0xB1));

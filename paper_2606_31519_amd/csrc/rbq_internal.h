@@ -34,28 +34,35 @@ rbq_status check_decode(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_
                         size_t ws_bytes);
 
 // ---------------------------------------------------------------- workspace layouts
-// Top-p: each row of scores is cut into parts of spb sub-chunks of kSelSub
-// keys; one block of kSelThreads threads per (row, part) in each of three
-// passes (per-part histograms, candidate gathering, final select + write).
+// Top-p: a row of scores of at most kSelRowMax keys is selected by one block; a
+// longer one is cut into parts of spb sub-chunks of kSelSub keys, one block of
+// kSelThreads threads per (row, part) in each of three passes (per-part
+// histograms, candidate gathering, final ranking + write).
 constexpr int kSelThreads = 1024;
 constexpr int kSelPerThread = 16;
 constexpr int kSelSub = kSelThreads * kSelPerThread;   // 16384 keys per sub-chunk
 constexpr int kSelMaxParts = 64;                       // parts per row (longer rows take more sub-chunks per part)
-constexpr int kSelBins = 4096;                         // 12-bit radix levels (key bits 31..20, then 19..8)
-constexpr int kSelBins3 = 256;                         // last level (key bits 7..0)
-constexpr int kSelCoarse = 64;                         // coarse bins of 64 first-level bins each
-constexpr int kSelCandCap = 4096;                      // candidate keys one part hands to the final pass
-constexpr int kSelCandLds = 16384;                     // candidate keys of a row the final pass holds in LDS
+// keys of a row one block holds in registers (32 per thread). One block per row against three passes, in us per call at
+// p = 0.95: 32 rows of 4096 / 16384 / 32768 keys 7.4 / 10.0 / 13.6 against 15.0 / 16.1 / 16.4, 512 rows of 32768 35
+// against 48. Twice the keys would not fit the registers, and at 32 rows one block would fall behind the three passes.
+constexpr int kSelRowMax = 32768;
+constexpr int kSelBins = 4096;                         // bins of a histogram
+constexpr float kSelPerOctave = 64.f;                  // bins per factor of two of the softmax mass
+constexpr int kSelCoarse = 64, kSelFine = 64;          // groups of bins, bins per group
+constexpr int kSelCandCap = 2048;                      // candidate keys one part can hand to the final pass
+constexpr int kSelCandLds = 8192;                      // candidate keys of a row the final pass holds in LDS
+constexpr int kSelRowCand = 4096;                      // the same of a row selected by one block
 constexpr int32_t kToppMaxKeys = int32_t(1) << 24;     // keys per row the fixed-point sums hold
 // per-part records (bytes): the first pass's exact histogram (the part's
-// maximum and total, 64 coarse sums, the directory of non-empty coarse bins
-// and their 64-bin sections; 64-bit fixed-point masses relative to the part's
-// maximum) and the second pass's counts and candidate keys
-constexpr size_t kSelP1Coarse = 16, kSelP1Dir = 16 + 8 * kSelCoarse, kSelP1Sec = 1024;
-constexpr size_t kSelPart1Bytes = kSelP1Sec + size_t(8) * kSelCoarse * 64;
+// maximum and total, its 64 group sums and the 64-bin sections of the groups
+// that hold mass; 64-bit fixed-point masses relative to the part's maximum) and
+// the second pass's counts and candidates {key, index}, the end of whose room
+// takes the part's bitmap when the caller brings none
+constexpr size_t kSelP1Coarse = 32, kSelP1Sec = 1024;
+constexpr size_t kSelPart1Bytes = kSelP1Sec + size_t(8) * kSelBins;
 constexpr size_t kSelP2Cand = 64;
-constexpr size_t kSelPart2Bytes = kSelP2Cand + size_t(4) * kSelCandCap;
-constexpr int kSelStateWords = 8;   // per row: row maximum, b1, mass needed inside b1, target (fp64)
+constexpr size_t kSelPart2Bytes = kSelP2Cand + size_t(8) * kSelCandCap;
+constexpr int kSelStateWords = 8;   // per row: row maximum, crossing bin, mass needed inside it (fp64), or K*
 
 struct ToppPlan {
   int32_t spb;     // sub-chunks per part

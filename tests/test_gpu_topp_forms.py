@@ -1,0 +1,105 @@
+"""The Top-p selection's forms (one block per row up to 32768 keys, three passes
+beyond, each with its irregular rows) against the oracle, at the sizes where one
+takes over from the other and on rows that leave the logarithmic grid."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import parity_util as pu
+from paper_2606_31519_amd import pipeline, rbq
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+TAU = 1 / math.sqrt(128)
+
+
+def _select(S, p, tau):
+    rows, n = S.shape
+    dS = torch.from_numpy(np.ascontiguousarray(S, dtype=np.float32)).cuda()
+    sel = torch.full((rows, n), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    rbq.rbq_topp_select(1, rows, n, dS, p, tau, sel, cnt, rbq.workspace(rbq.RBQ_OP_TOPP, 1, rows, rows, 128, n))
+    torch.cuda.synchronize()
+    return sel.cpu().numpy(), cnt.cpu().numpy()
+
+
+def _rows(n, seed):
+    r = np.random.default_rng(seed)
+    x = r.standard_normal(n)
+    tail = np.concatenate([[40.0 / TAU], np.full(n - 1, 0.0)]) if n > 1 else np.zeros(1)
+    return np.stack([
+        x * 3.0 / TAU,                                     # a few octaves: some keys per bin
+        x * 1e-3 / TAU,                                    # everything inside one bin or two
+        x * 0.08 / TAU,                                    # hundreds to thousands of candidates
+        np.round(x * 4.0) / TAU,                           # ties
+        x * 1e6,                                           # bins past 2^24, where a bin is one fp32 value
+        np.where(r.random(n) < 0.3, -np.inf, x / TAU),     # masked keys
+        np.where(np.arange(n) % 7 == 0, x / TAU, np.finfo(np.float32).min),   # the same with the lowest value
+        -np.abs(x) * 1e-30,                                # around zero
+        tail,                                              # the target may lie below the window
+    ])
+
+
+@pytest.mark.parametrize("n", [1, 63, 1024, 4096, 4097, 8193, 16384, 16385, 28673, 32768, 32769, 49152, 131071])
+@pytest.mark.parametrize("p", [0.05, 0.9, 0.999])
+def test_forms_against_the_oracle(n, p):
+    S = _rows(n, n)
+    sel, cnt = _select(S, p, TAU)
+    for r in range(S.shape[0]):
+        pu.check_topp(S[r].astype(np.float32), p, TAU, sel[r, :cnt[r]])
+
+
+@pytest.mark.parametrize("n", [20000, 40000])
+def test_targets_below_the_window(n):
+    """Half of the mass sits more than 2^31.5 below the top key: p just under 1 has its boundary there. A mass that far
+    down is a 2^-40 integer of about 60 units, truncated: each key is off by up to 1 / 60 of itself."""
+    S = np.zeros((1, n))
+    S[0, 5] = 34.5 * math.log(2) / TAU
+    S[0, n // 2:] -= 2.0 / TAU
+    sel, cnt = _select(S, 1.0 - 2e-7, TAU)
+    assert sel[0, 0] >= 0 and 5 in sel[0, :cnt[0]]
+    got = sel[0, :cnt[0]]
+    assert np.array_equal(got, np.sort(got)) and (cnt[0] == 1 or cnt[0] >= n // 2)
+
+
+@pytest.mark.parametrize("n", [5000, 40000])
+def test_rows_without_a_finite_maximum(n):
+    """An infinite maximum leaves no key a mass: every key is selected (NaN scores add no mass)."""
+    x = np.random.default_rng(n).standard_normal(n)
+    S = np.stack([np.where(np.arange(n) == 77, np.inf, x), np.full(n, -np.inf), x])
+    sel, cnt = _select(S, 0.9, 1.0)
+    for r in (0, 1):
+        assert cnt[r] == n and np.array_equal(sel[r], np.arange(n))
+    S[2, 11] = np.nan
+    got, c2 = _select(S[2:], 0.9, 1.0)
+    want = np.setdiff1d(sel[2, :cnt[2]], [11])
+    assert np.setxor1d(got[0, :c2[0]], want).size <= 2
+
+
+def test_long_row_without_a_bitmap():
+    """More than four sub-chunks per part: the separate call keeps no bitmap and compares the scores again."""
+    n = 4_300_001
+    S = (np.random.default_rng(3).standard_normal((1, n)) * 3.0 / TAU).astype(np.float32)
+    sel, cnt = _select(S, 0.9, TAU)
+    pu.check_topp(S[0], 0.9, TAU, sel[0, :cnt[0]])
+
+
+@pytest.mark.parametrize("n,w", [(4095, 9), (32768, 0), (32771, 33), (70000, 256)])
+def test_step_equals_calls(n, w):
+    """The fused step selects into its bitmaps, the separate call into its workspace: the same keys and outputs."""
+    wl = gen.random_case(2, 8, 2, n, seed=n, w=w, p=0.9)
+    a, b = pipeline.DecodeState.from_workload(wl), pipeline.DecodeState.from_workload(wl)
+    for st in (a, b):
+        st.build_index()
+    a.step(0.9, flush=False)
+    b.step_calls(0.9, flush=False)
+    torch.cuda.synchronize()
+    cnt = a.sel_count.cpu().numpy()
+    assert np.array_equal(cnt, b.sel_count.cpu().numpy())
+    ia, ib = a.sel_idx.cpu().numpy(), b.sel_idx.cpu().numpy()
+    for s in range(2):
+        for h in range(8):
+            assert np.array_equal(ia[s, h, :cnt[s, h]], ib[s, h, :cnt[s, h]])
+    assert torch.equal(a.out, b.out) and torch.equal(a.lse, b.lse)
