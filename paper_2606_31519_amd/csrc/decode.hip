@@ -25,6 +25,14 @@
 //           bytes of 4 rows and pairs rows with v_perm), 8 column blocks of 16
 //           dimensions, accumulated in fp32.
 // The next group's loads are issued before the current group is computed.
+// What a block does besides the gather (staging the queries, listing its rows,
+// merging its waves) bounds short contexts and small selections, so each piece
+// is one short pass: a thread forms all three parts of 8 query dimensions, a
+// head's mask of a word of 64 positions is the lane mask of one select, lists
+// are padded so that a lane reads its four rows and their heads at once, and the
+// merge takes four dimensions per thread. 32 query / 8 KV heads, the block's time
+// without its gather: 4K keys 3.4 -> 2.5 us, 128K keys 6 -> 4.6 us (of 42), groups
+// of 8 heads 13 -> 10 us; the sparse call of the 4K step 6.9 -> 5.5 us.
 // fp32 K/V (decode_vec_kernel, small workloads): the same split with vector
 // ALU dots (lane = row for the logits, lane = 2 dimensions for the values).
 // Waves merge in LDS; the block writes (m, l, acc[D]) per head; a combine
@@ -51,6 +59,8 @@ constexpr int kBmWords = kDecodeChunk / 32;                       // words of th
 constexpr int kListRounds = (kDecodeChunk + kDecodeFoldMax + kDThreads - 1) / kDThreads;
 constexpr int kListCap = kListRounds * kDThreads;                 // list positions (indexed + folded window)
 static_assert(kListCap == kDecodeListCap, "the split sizing on the host assumes this list capacity");
+constexpr int kListPad = 16;                                      // a list ends on a whole group of rows
+static_assert(kListCap % kListPad == 0, "the padding fits");
 constexpr float kLn2 = 0.69314718055994531f;
 __device__ __forceinline__ float wmax64(float v) { v = max32(v); return fmaxf(v, __shfl_xor(v, 32, kWave)); }
 __device__ __forceinline__ float wsum64(float v) { v = sum32(v); return v + __shfl_xor(v, 32, kWave); }
@@ -148,8 +158,9 @@ __device__ __forceinline__ HeadCounts<G> load_head_counts(const int32_t* __restr
 // group of the positions in [c0, c1) that each head selected, in ascending
 // order, with a bit mask of the heads that selected each entry, followed by
 // the nwin window rows folded into the split (every head; list positions
-// c1 - c0 + i, rows c1 + wshift + i). Returns the
-// number of entries (block-uniform). All threads of the block must call it.
+// c1 - c0 + i, rows c1 + wshift + i), and padded to whole groups of kListPad
+// entries with a listed row that no head takes. Returns the number of entries without
+// the padding (block-uniform). All threads of the block must call it.
 // The list is ranked from the split's 16 words of 64 positions per head: the
 // selection's bitmaps themselves when given (sel_mask != NULL, [rows][mask_words]
 // words of 64 keys, c0 a multiple of 64); otherwise each wave finds the part
@@ -245,10 +256,11 @@ __device__ __forceinline__ int build_union_list(const int32_t* __restrict__ sel_
   for (int v = wave; v < kBmWords / 2; v += kWaves) {   // (wave-uniform)
     const unsigned long long uw = readlane_u64(u, v);
     const int off = __builtin_amdgcn_readlane(int(excl), v);
-    uint32_t mk = 0u;
+    uint32_t mk = 0u;   // (a head's word is the lane mask itself: one select per head)
 #pragma unroll
-    for (int g = 0; g < G; ++g) mk |= uint32_t((readlane_u64(mw.w[g / 4], (g % 4) * 16 + v) >> lane) & 1ull) << g;
-    if ((uw >> lane) & 1ull) {
+    for (int g = 0; g < G; ++g)
+      mk |= __builtin_amdgcn_inverse_ballot_w64(readlane_u64(mw.w[g / 4], (g % 4) * 16 + v)) ? 1u << g : 0u;
+    if (__builtin_amdgcn_inverse_ballot_w64(uw)) {
       const int o = off + int(__builtin_amdgcn_mbcnt_hi(uint32_t(uw >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(uw), 0u)));
       lst[o] = c0 + 64 * v + lane;
       hmask[o] = uint16_t(mk);
@@ -258,6 +270,15 @@ __device__ __forceinline__ int build_union_list(const int32_t* __restrict__ sel_
     for (int i = lane; i < nwin; i += kWave) {   // the folded window rows, every head
       lst[nidx + i] = c1 + wshift + i;
       hmask[nidx + i] = uint16_t((1u << G) - 1u);
+    }
+    // up to a whole group: a listed row once more, for no head (a row that is not
+    // listed may hold anything, and its values would meet probabilities of zero)
+    const int v0 = __builtin_ctzll(__ballot(u != 0ull) | (1ull << 63)) & 15;
+    const unsigned long long w0 = readlane_u64(u, v0);
+    const int o = nidx + nwin + lane;
+    if (lane < kListPad && o < (nidx + nwin + kListPad - 1) / kListPad * kListPad) {
+      lst[o] = nidx > 0 ? c0 + 64 * v0 + __builtin_ctzll(w0 | (1ull << 63)) : c1 + wshift;
+      hmask[o] = 0;
     }
   }
   __syncthreads();
@@ -503,6 +524,8 @@ __global__ __launch_bounds__(kDThreads) void decode_vec_kernel(
 
 // ---------------------------------------------------------------- bf16 K/V on the matrix cores
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGroupRows = 16;   // rows per MFMA group
@@ -547,48 +570,57 @@ constexpr int kSkipOffset = 0x7FFFFF00;
 constexpr int kStream = 2;   // cache-policy bits of the K / V buffer loads: nt
 constexpr int kStreamDenNum = 1, kStreamDenDen = 3;   // a third of the block's positions
 
-template <bool SPARSE>
-__device__ __forceinline__ int row_at(int e, bool list, const RowMap& rm, const int32_t* lst) {
-  if constexpr (SPARSE) {
-    const int lv = lst[e];
-    return list ? lv : rm.at(e);
-  }
-  return rm.at(e);
-}
-
 template <bool SPARSE, int D, int CP>
-__device__ __forceinline__ void load_group_k(GroupLoads<D>& d, int grp, bool skip, int U, const RowMap& rm, bool list,
+__device__ __forceinline__ void load_group_k(GroupLoads<D>& d, int grp, bool skip, int U, const RowMap& rm,
                                              const int32_t* lst, __amdgpu_buffer_rsrc_t Kr, int x, int j) {
-  const int e0 = grp * kGroupRows;
-  const int ek = e0 + x < U ? e0 + x : e0;
-  const int pk = row_at<SPARSE>(ek, list, rm, lst);
+  const int e = grp * kGroupRows + x;
+  int pk;
+  if constexpr (SPARSE) pk = lst[e];
+  else pk = rm.at(e < U ? e : e - x);
   const int off = skip ? kSkipOffset : pk * (D * 2) + 16 * j;
 #pragma unroll
   for (int kb = 0; kb < D / 32; ++kb) d.k[kb] = __builtin_amdgcn_raw_buffer_load_b128(Kr, off + 64 * kb, 0, CP);
 }
 
 template <bool SPARSE, int G, int D, int CP>
-__device__ __forceinline__ void load_group_v(GroupLoads<D>& d, int grp, bool skip, int U, const RowMap& rm, bool list,
-                                             const int32_t* lst, const uint16_t* hmask,
-                                             __amdgpu_buffer_rsrc_t Vr, int x, int j) {
-  const int e0 = grp * kGroupRows;
-  uint32_t mk = 0;
+__device__ __forceinline__ void load_group_v(GroupLoads<D>& d, int grp, bool skip, int U, const RowMap& rm,
+                                             const int32_t* lst, const uint16_t* hmask, __amdgpu_buffer_rsrc_t Vr,
+                                             int x, int j) {
+  const int e0 = grp * kGroupRows + 4 * j;   // this lane's four entries
+  i32x4 row;
+  if constexpr (SPARSE) {
+    row = *reinterpret_cast<const i32x4*>(lst + e0);
+    const u32x2 hm = *reinterpret_cast<const u32x2*>(hmask + e0);   // (x < 16: bits past the heads are clear)
+    const uint32_t a = (hm.x >> x) & 0x10001u, b = (hm.y >> x) & 0x10001u;
+    d.mk = (a | (a >> 15) | (b << 2) | (b >> 13)) & 15u;
+  } else {
+    uint32_t mk = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool valid = e0 + i < U;
+      row[i] = rm.at(valid ? e0 + i : e0 - 4 * j);
+      mk |= uint32_t(valid && x < G) << i;
+    }
+    d.mk = mk;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int e = e0 + 4 * j + i;
-    const bool valid = e < U;
-    const int ev = valid ? e : e0;
-    const int pv = row_at<SPARSE>(ev, list, rm, lst);
-    const int off = skip ? kSkipOffset : pv * (D * 2) + (D / 8) * x;
+    const int off = skip ? kSkipOffset : row[i] * (D * 2) + (D / 8) * x;
     if constexpr (D == 64)
       d.v[i] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(Vr, off, 0, CP));
     else
       d.v[i] = __builtin_amdgcn_raw_buffer_load_b128(Vr, off, 0, CP);
-    bool on = valid && x < G;
-    if constexpr (SPARSE) on = on & (!list | bool((hmask[ev] >> x) & 1u));
-    mk |= uint32_t(on) << i;
   }
-  d.mk = mk;
+}
+
+// x = hi + mid + lo in bf16 parts, each rounded to nearest even
+__device__ __forceinline__ void split3(const f32x8 x, bf16x8* p) {
+  f32x8 r = x;
+#pragma unroll
+  for (int t = 0; t < kQParts; ++t) {
+    p[t] = __builtin_convertvector(r, bf16x8);
+    if (t + 1 < kQParts) r -= __builtin_convertvector(p[t], f32x8);
+  }
 }
 
 template <bool SPARSE, int G, bool RAGGED, int D = kHeadDim>
@@ -606,11 +638,11 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
   constexpr int VB = D / 32;                      // value blocks per parity (D / 16 columns per lane)
   __shared__ u32x4 qB[KB][kQOps][kWave];          // B operands of the logits product
   __shared__ uint32_t bm[SPARSE ? G : 1][kBmWords];
-  __shared__ int32_t lst[SPARSE ? kListCap : 1];
-  __shared__ uint16_t hmask[SPARSE ? kListCap : 1];
+  __shared__ __attribute__((aligned(16))) int32_t lst[SPARSE ? kListCap : 1];
+  __shared__ __attribute__((aligned(16))) uint16_t hmask[SPARSE ? kListCap : 1];
   __shared__ int rng_lo[G], rng_hi[G];
   __shared__ float sm[kDWaves][G], sl[kDWaves][G];
-  __shared__ float sacc[kDWaves][G][D];
+  __shared__ __attribute__((aligned(16))) float sacc[kDWaves][G][D];
 
   const int split = RAGGED ? blockIdx.y : blockIdx.x;   // (ragged grids are split-major)
   const int bh = RAGGED ? blockIdx.x : blockIdx.y;
@@ -660,34 +692,18 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
 
   // query operands, lane (column c, quarter jj) of k-block kb = dims 32 kb + 8 jj .. +8.
   // G <= 4: one operand per k-block, column c = part * G + head; otherwise one
-  // operand per (k-block, part), column c = head.
-  for (int e = threadIdx.x; e < KB * kQOps * kWave; e += kDThreads) {
-    const int kb = e / (kQOps * kWave), op = (e / kWave) % kQOps, ln = e % kWave;
-    const int c = ln & 15, jj = ln >> 4;
-    const int h = kPackedQ ? c % G : c;
-    const int prt = kPackedQ ? c / G : op;
-    uint32_t wds[4] = {0u, 0u, 0u, 0u};
-    if (h < G && prt < kQParts) {
-      // both 16-byte loads are issued before any use (a loop over the part index
-      // with a run-time bound otherwise serialises one load per element)
-      const f32x4* qp = reinterpret_cast<const f32x4*>(q + int64_t(row0 + h) * D + 32 * kb + 8 * jj);
-      const f32x4 qa = qp[0], qb = qp[1];
-      const float qv[8] = {qa.x, qa.y, qa.z, qa.w, qb.x, qb.y, qb.z, qb.w};
+  // operand per (k-block, part), column c = head. (Columns without a head stay
+  // unwritten: each column of the product depends on its own column only, and
+  // those are masked.) A thread forms the three parts of 8 dimensions of a head.
+  for (int e = threadIdx.x; e < G * (D / 8); e += kDThreads) {
+    const int h = e / (D / 8), ch = e % (D / 8);
+    const f32x4* qp = reinterpret_cast<const f32x4*>(q + int64_t(row0 + h) * D + 8 * ch);
+    const f32x8 qv = __builtin_shufflevector(qp[0], qp[1], 0, 1, 2, 3, 4, 5, 6, 7) * scale_log2e;
+    bf16x8 parts[kQParts];
+    split3(qv, parts);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float r = qv[i] * scale_log2e;
-        uint32_t bits = 0u;
-#pragma unroll
-        for (int t = 0; t < kQParts; ++t) {   // part prt = the residual after prt subtractions
-          if (t <= prt) {
-            bits = bf16_bits(r);
-            r -= bf16_val(bits);
-          }
-        }
-        wds[i >> 1] |= bits << (16 * (i & 1));
-      }
-    }
-    qB[kb][op][ln] = u32x4{wds[0], wds[1], wds[2], wds[3]};
+    for (int t = 0; t < kQParts; ++t)
+      qB[ch / 4][kPackedQ ? 0 : t][16 * (ch % 4) + (kPackedQ ? t * G + h : h)] = __builtin_bit_cast(u32x4, parts[t]);
   }
 
   int U;
@@ -695,10 +711,15 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
     U = build_union_list<G, kDThreads, kPreMask>(sel_idx, sel_mask, mask_words, row0, n, c0, c1, nwin, wrow0 - c1, bm, lst, hmask, rng_lo, rng_hi,
                                        mword, hcount);
   } else {
-    __syncthreads();
     U = (c1 - c0) + nwin;
+    if constexpr (SPARSE) {   // window rows of their own: every head takes all of them
+      for (int e = threadIdx.x; e < (U + kListPad - 1) / kListPad * kListPad; e += kDThreads) {
+        lst[e] = c0 + min(e, U - 1);
+        hmask[e] = uint16_t(e < U ? (1u << G) - 1u : 0u);
+      }
+    }
+    __syncthreads();
   }
-  const bool list = SPARSE && !window;
   const RowMap rm{c0, c1 - c0, RAGGED && nwin > 0 ? wrow0 - c1 : 0};
 
   float m = -INFINITY, lsum = 0.f;      // head x's running max (uniform over j) and this lane's partial sum
@@ -717,8 +738,8 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
   GroupLoads<D> cur;
   int grp = wave;
   if (grp < ngroups) {
-    load_group_k<SPARSE, D, CP>(cur, grp, false, U, rm, list, lst, Kr, x, j);
-    load_group_v<SPARSE, G, D, CP>(cur, grp, false, U, rm, list, lst, hmask, Vr, x, j);
+    load_group_k<SPARSE, D, CP>(cur, grp, false, U, rm, lst, Kr, x, j);
+    load_group_v<SPARSE, G, D, CP>(cur, grp, false, U, rm, lst, hmask, Vr, x, j);
   }
   while (grp < ngroups) {
     const int nxt = grp + kDWaves;
@@ -738,7 +759,7 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
         s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, qp[(kb * kQOps + op) * kWave]), s,
                                                     0, 0, 0);
     }
-    load_group_k<SPARSE, D, CP>(cur, last ? grp : nxt, last, U, rm, list, lst, Kr, x, j);
+    load_group_k<SPARSE, D, CP>(cur, last ? grp : nxt, last, U, rm, lst, Kr, x, j);
     if constexpr (kPackedQ) {
       // column h + G and h + 2G hold the mid and lo parts of head h's logits
       // (each element goes through an opaque copy first: hipcc 7.2 miscompiles
@@ -811,7 +832,7 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
         acc[t][par] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_lo, bv, acc[t][par], 0, 0, 0);
       }
     }
-    load_group_v<SPARSE, G, D, CP>(cur, last ? grp : nxt, last, U, rm, list, lst, hmask, Vr, x, j);
+    load_group_v<SPARSE, G, D, CP>(cur, last ? grp : nxt, last, U, rm, lst, hmask, Vr, x, j);
     grp = nxt;
   }
   };
@@ -830,35 +851,35 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
     const int h = 4 * j + i;
     if (h < G) {
 #pragma unroll
-      for (int t = 0; t < VB; ++t) {
-        sacc[wave][h][(D / 16) * x + 2 * t] = acc[t][0][i];
-        sacc[wave][h][(D / 16) * x + 2 * t + 1] = acc[t][1][i];
-      }
+      for (int t = 0; t < VB; t += 2)
+        *reinterpret_cast<f32x4*>(&sacc[wave][h][(D / 16) * x + 2 * t]) =
+            f32x4{acc[t][0][i], acc[t][1][i], acc[t + 1][0][i], acc[t + 1][1][i]};
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < G * (D + 2); e += kDThreads) {
-    const int g = e / (D + 2);
-    const int k = e - g * (D + 2);
+  // (four dimensions per thread; the partial states are 8-byte aligned)
+  for (int e = threadIdx.x; e < G * (D / 4); e += kDThreads) {
+    const int g = e / (D / 4), d4 = e % (D / 4);
     float M = -INFINITY;
 #pragma unroll
     for (int v = 0; v < kDWaves; ++v) M = fmaxf(M, sm[v][g]);
-    float r;
-    if (k == 0) {
-      r = M;
-    } else {
-      r = 0.f;
-      if (M != -INFINITY) {
+    f32x4 r = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+    if (M != -INFINITY) {
 #pragma unroll
-        for (int v = 0; v < kDWaves; ++v) {
-          if (sm[v][g] != -INFINITY) {
-            const float sc = __builtin_amdgcn_exp2f(sm[v][g] - M);
-            r = fmaf(k == 1 ? sl[v][g] : sacc[v][g][k - 2], sc, r);
-          }
+      for (int v = 0; v < kDWaves; ++v) {
+        if (sm[v][g] != -INFINITY) {
+          const float sc = __builtin_amdgcn_exp2f(sm[v][g] - M);
+          const f32x4 a = *reinterpret_cast<const f32x4*>(&sacc[v][g][4 * d4]);
+          r = f32x4{fmaf(a.x, sc, r.x), fmaf(a.y, sc, r.y), fmaf(a.z, sc, r.z), fmaf(a.w, sc, r.w)};
+          l = fmaf(sl[v][g], sc, l);
         }
       }
     }
-    part[(int64_t(row0 + g) * total_splits + split) * (D + 2) + k] = r;
+    f32x2* o = reinterpret_cast<f32x2*>(part + (int64_t(row0 + g) * total_splits + split) * (D + 2));
+    if (d4 == 0) o[0] = f32x2{M, l};
+    o[1 + 2 * d4] = f32x2{r.x, r.y};
+    o[2 + 2 * d4] = f32x2{r.z, r.w};
   }
 }
 
