@@ -5,9 +5,9 @@
 //
 // The rotation is the only dense contraction on the path, so it runs on the
 // matrix cores: long runs of keys as described at encode_long_kernel, up to 4096
-// keys per head (every window of the lazy update) with v_mfma_f32_32x32x2_f32 (fp32 in, fp32 accumulate: the sign
-// decisions need fp32 accuracy, bf16 products of P would flip signs of small
-// components). Each wave keeps its 32 output columns of P in registers as the
+// keys per head (every window of the lazy update) with v_mfma_f32_32x32x2_f32
+// (fp32 in, fp32 accumulate: the sign decisions need fp32 accuracy, bf16 products
+// of P would flip signs of small components). Each wave keeps its 32 output columns of P in registers as the
 // MFMA B operands (64 floats per lane, all requested at once), and a tile of
 // 32 centred keys is staged in LDS. In the 32x32 accumulator layout lane l
 // holds output column l % 32, so one wave ballot of (r > 0) over a register
@@ -114,12 +114,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(EncodeArgs ea) {
 // does the same for its largest entry, and both are split into two fp16 parts,
 // hi + mid (22 bits of each value); then
 //   r = (hm + mh) + hh,
-// three products that are exact in fp32, the small ones summed first. What is left out (the mid x mid products and the bits past the
-// 22nd) is about 7e-8 of a component's rms, and there are 8 roundings of the large
-// sum where the fp32 form has 65: against 64 bits the components are off by
-// 1.1e-7 of their rms instead of 1.45e-7, the factors by 7.3e-8 instead of 9.3e-8.
+// three products that are exact in fp32, the small ones summed first. What is left
+// out (the mid x mid products and the bits past the 22nd) is about 7e-8 of a
+// component's rms, and there are 8 roundings of the large sum where the fp32 form
+// has 65: against 64 bits the components are off by 1.1e-7 of their rms instead of
+// 1.45e-7, the factors by 7.3e-8 instead of 9.3e-8, and no sign is (kNearZero).
 // (Three bf16 parts and six products were off by 0.7e-7, in 200 us where this
-// form takes 123.)
+// form took 123 before the signs' second look, which costs 2.)
 //
 // The product is taken transposed, r^T = P^T x^T: a lane then holds 16 output
 // dimensions of ONE key (key l % 32 of its tile in lane l), so a key's sign word,
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(EncodeArgs ea) {
 //
 // Bound: the matrix cores and the vector ALUs that centre and split, at the clock
 // the card holds under them (1.5 to 1.6 GHz measured). 8 heads x 130816 bf16 keys,
-// D = 128: 123 us, the fp32 form 336; with the centroid 153 us a call, before 390.
+// D = 128: 125 us, the fp32 form 336; with the centroid 158 us a call, before 390.
 // (fp32 keys, whose coming tile takes twice the registers: 8 waves)
 constexpr int long_waves(int dt) { return dt == RBQ_BF16 ? 12 : 8; }
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -163,6 +164,25 @@ __device__ __forceinline__ float max_abs8(f32x8 x, float m) {   // (pairs: one t
   for (int i = 0; i < 8; i += 2) m = fmaxf(fmaxf(m, fabsf(x[i])), fabsf(x[i + 1]));
   return m;
 }
+// Components this close to zero are formed again in 64 bits for their sign: in the
+// scaled units about 2e-6 of a component's rms (1e-6 for keys with all components
+// alike), ten times the rounding error, met in one of 150 tiles of 32 keys. More than
+// two exact zeros among 16 components are no chance (a key at the centroid, sparse
+// keys under a sparse P) and stay zeros.
+// Of 2.8e9 bits against 64 bits 68 were off without this, 80 in the fp32 form, and
+// none are with it.
+constexpr float kNearZero = 1024.f;
+template <int DT, int D>
+__device__ __forceinline__ double component_f64(const char* key, const float* ck, const float* p) {
+  double r = 0.0;
+#pragma unroll 16
+  for (int d = 0; d < D; ++d) {
+    const float x = DT == RBQ_BF16 ? __uint_as_float(uint32_t(reinterpret_cast<const uint16_t*>(key)[d]) << 16)
+                                   : reinterpret_cast<const float*>(key)[d];
+    r = fma(double(x) - double(ck[d]), double(p[d * D]), r);
+  }
+  return r;
+}
 // x of this lane + x of the lane 32 away
 __device__ __forceinline__ float sum_halves(float x) { return x + __shfl_xor(x, 32, kWave); }
 
@@ -177,6 +197,7 @@ __global__ __launch_bounds__(long_waves(DT) * kWave) void encode_long_kernel(Enc
   __shared__ float ck_s[D], cq_s[D];
   __shared__ float red[kLongWaves];
   __shared__ int next_s;
+  __shared__ uint16_t near_s[W][kLongWaves][kWave];   // (a lane's own: no wait between its write and its read)
   const int bh = blockIdx.x / blocks_per_head, bx = blockIdx.x % blocks_per_head;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
   const int key_l = lane & 31, half = lane >> 5;
@@ -279,6 +300,7 @@ __global__ __launch_bounds__(long_waves(DT) * kWave) void encode_long_kernel(Enc
 
     const int key = tile * 32 + key_l;
     uint32_t word[W];
+    uint32_t open = 0u;   // words (of any lane's key) with a component whose sign is still open
     float absum = 0.f;
 #pragma unroll 1
     for (int jp = 0; jp < W; jp += 2) {   // two words at a time: two chains of products
@@ -312,10 +334,13 @@ __global__ __launch_bounds__(long_waves(DT) * kWave) void encode_long_kernel(Enc
         __builtin_amdgcn_sched_barrier(0);
       }
       // register i of a[j]: -r of dimension 32 (jp + j) + 8 (i / 4) + 4 half + i % 4 of this lane's key
+      float low = kNearZero;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         uint32_t bits = 0u;
         float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) low = fminf(fminf(low, fabsf(a[j][i])), fabsf(a[j][i + 1]));
 #pragma unroll
         for (int i = 15; i >= 0; --i) {
           const float r = a[j][i];
@@ -333,6 +358,34 @@ __global__ __launch_bounds__(long_waves(DT) * kWave) void encode_long_kernel(Enc
         bits |= uint32_t(__shfl_xor(int(bits), 32, kWave));
 #pragma unroll
         for (int w = 0; w < W; ++w) word[w] = w == jp + j ? bits : word[w];
+      }
+      if (__any(low < kNearZero)) {
+        open |= 1u << jp;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          uint32_t m = 0u, z = 0u;
+#pragma unroll
+          for (int i = 15; i >= 0; --i) m = (m << 1) | uint32_t(fabsf(a[j][i]) < kNearZero);
+#pragma unroll
+          for (int i = 15; i >= 0; --i) z = (z << 1) | uint32_t(a[j][i] == 0.f);
+          near_s[jp + j][wave][lane] = uint16_t(__popc(z) > 2 ? m & ~z : m);
+        }
+      }
+    }
+    if (open != 0u) {   // wave-uniform
+      int row = min(key, n_new - 1), half4 = 4 * half;
+      asm volatile("" : "+v"(row), "+v"(half4));   // (formed here, not kept in registers through the products)
+      const char* kp = static_cast<const char*>(ea.keys) + int64_t(bh) * ea.keys_ld * D * kElem + int64_t(row) * D * kElem;
+      const uint32_t own = 0x0f0f0f0fu << half4;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        if (!((open >> (w & ~1)) & 1u)) continue;
+        for (uint32_t near = near_s[w][wave][lane]; near; near &= near - 1) {
+          const int i = __builtin_ctz(near), d = 8 * (i / 4) + half4 + i % 4;
+          const uint32_t one = component_f64<DT, D>(kp, ck_s, ea.P + 32 * w + d) > 0.0 ? 1u : 0u;
+          word[w] = (word[w] & ~(1u << d)) | (one << d);
+        }
+        word[w] = (word[w] & own) | uint32_t(__shfl_xor(int(word[w] & own), 32, kWave));
       }
     }
     absum = ldexpf(sum_halves(absum), -xexp - pexp);

@@ -83,3 +83,25 @@ def test_zero_components_and_keys_at_the_centroid():
     assert kfac[0, 0, 7, 0] == 0 and kfac[0, 0, 11, 0] == 0
     # the parts hold 22 bits: each component within 2^-21 of itself
     assert ((rot[0, 0] - K[0, 0].float()).abs() <= 2.0 ** -21 * K[0, 0].float().abs()).all()
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [40000, 4100])
+def test_every_sign_is_that_of_64_bits(D, kv, n):
+    """Components within rounding of zero are formed again in 64 bits: no bit differs from the sign there, with some
+    components of each key made small on purpose (n = 4100: every key, through P's columns)."""
+    H = 6
+    g = torch.Generator(device="cuda").manual_seed(n + D)
+    P = torch.from_numpy(gen.haar_rotation(D)).cuda()
+    K = torch.randn(1, H, n, D, device="cuda", generator=g)
+    if n == 4100:   # r ~ 1e-7 in two components of every key, on either side of zero
+        r = torch.randn(1, H, n, D, device="cuda", generator=g).double()
+        r[..., 5] *= 1e-7
+        r[..., D - 2] *= 1e-7
+        K = (r @ P.double().T).float()
+    K = K.to(torch.bfloat16 if kv == "bf16" else torch.float32).contiguous()
+    ck, codes, _, _, _ = _encode(K, P, None, rot=False)
+    r = (K[0].double() - ck[0].double()[:, None]) @ P.double()
+    bits = torch.stack([(codes[0, :, :, d // 32] >> (d % 32)) & 1 for d in range(D)], 2).bool()
+    assert int((bits != (r > 0)).sum()) == 0
