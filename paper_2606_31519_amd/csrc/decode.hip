@@ -42,7 +42,8 @@
 // (clamped to [0, n]) and seq_w[b] window rows (clamped to [0, w]; all w when
 // seq_w is NULL), the window being its cache tail, rows [seq_n[b], seq_n[b] +
 // seq_w[b]) of K / V (K_loc = K, loc_ld = cap). The grid is sized by n and w
-// and launched split-major; a sequence's window is spread over its own splits,
+// and launched split-major (many blocks of the sparse call: the densest
+// sequences first, see sequence_of_rank); a sequence's window is spread over its own splits,
 // and a split past its rows writes an empty partial state and leaves.
 #include <cmath>
 #include <type_traits>
@@ -112,10 +113,9 @@ __device__ __forceinline__ void wave_lower_bounds(const int32_t* __restrict__ a,
 
 // This lane's words of the split's selection bitmaps: word l % 16 (keys
 // c0 + 64 (l % 16) .. + 64) of heads l / 16 + 4k. Every wave of the block reads
-// the same words; for small groups they are requested at the start of the
-// kernel so that the loads overlap the query staging. (Bits past the split's
-// last position are cleared where the words are used, so that no wait for the
-// loads is placed here.)
+// the same words; the matrix-core kernel requests them at its start so that the
+// loads overlap the query staging. (Bits past the split's last position are
+// cleared where the words are used, so that no wait for the loads is placed here.)
 template <int G>
 struct MaskWords {
   unsigned long long w[(G + 3) / 4];
@@ -623,6 +623,35 @@ __device__ __forceinline__ void split3(const f32x8 x, bf16x8* p) {
   }
 }
 
+// The sequence that the blocks of rank r take: sequences by the share of their
+// indexed keys that is selected (of one query head each of up to 8 KV heads),
+// the densest first. Lane b weighs sequence b (batch <= 64); its n_b in `own`.
+// Blocks of dense sequences take several times as long as the others (16 sequences
+// of 2K to 32K keys, p 0.5 to 0.95: 37 to 46 us against 7 to 13), and started last
+// they run on alone: 72 us for that launch, densest first 58. The order costs a block
+// one more round of loads, so launches that are resident at once keep theirs.
+constexpr int kOrderMinBlocks = 1024;   // 4 blocks on each of 256 CUs
+constexpr int kOrderHeads = 8;
+__device__ __forceinline__ int sequence_of_rank(int r, int batch, int n, int Hq, int Hkv,
+                                                const int32_t* __restrict__ sel_count,
+                                                const int32_t* __restrict__ seq_n, int& own) {
+  const int lane = lane_id(), b = min(lane, batch - 1), G = Hq / Hkv;
+  own = min(max(seq_n[b], 0), n);
+  int cnt[kOrderHeads];
+#pragma unroll
+  for (int k = 0; k < kOrderHeads; ++k) cnt[k] = sel_count[b * Hq + k * Hkv / kOrderHeads * G];
+  int sum = 0;
+#pragma unroll
+  for (int k = 0; k < kOrderHeads; ++k) sum += cnt[k];
+  const float dens = float(sum) / float(max(own, 1));
+  int rank = 0;
+  for (int o = 0; o < batch; ++o) {
+    const float d = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(__float_as_uint(dens)), o)));
+    rank += d > dens || (d == dens && o < lane) ? 1 : 0;
+  }
+  return __builtin_ctzll(__ballot(lane < batch && rank == r) | (1ull << 63));
+}
+
 template <bool SPARSE, int G, bool RAGGED, int D = kHeadDim>
 __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
     const float* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, int cap, int n,
@@ -630,7 +659,7 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
     const unsigned long long* __restrict__ sel_mask, int mask_words, const uint16_t* __restrict__ K_loc,
     const uint16_t* __restrict__ V_loc, int64_t loc_ld, int w, int chunk, int idx_splits, int total_splits,
     int fold_s0, int fold_wq, float scale_log2e, float* __restrict__ part, int Hq, int Hkv,
-    const int32_t* __restrict__ seq_n, const int32_t* __restrict__ seq_w) {
+    const int32_t* __restrict__ seq_n, const int32_t* __restrict__ seq_w, int ordered) {
   static_assert(G >= 1 && G <= 16, "the MFMA tiles hold at most 16 heads");
   constexpr bool kPackedQ = kQParts * G <= 16;
   constexpr int kQOps = kPackedQ ? 1 : kQParts;
@@ -644,15 +673,41 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
   __shared__ float sm[kDWaves][G], sl[kDWaves][G];
   __shared__ __attribute__((aligned(16))) float sacc[kDWaves][G][D];
 
-  const int split = RAGGED ? blockIdx.y : blockIdx.x;   // (ragged grids are split-major)
-  const int bh = RAGGED ? blockIdx.x : blockIdx.y;
-  const int b = bh / Hkv, hk = bh - b * Hkv;
+  // ragged grids are split-major (ordered: a sequence's blocks after the other's, ordered = batch)
+  int split = RAGGED ? blockIdx.y : blockIdx.x;
+  int bh = RAGGED ? blockIdx.x : blockIdx.y;
+  int b = bh / Hkv, hk = bh - b * Hkv;
+  int own_n = 0;
+  if (RAGGED && SPARSE && ordered) {
+    const int per = Hkv * total_splits, id = blockIdx.y * gridDim.x + blockIdx.x, r = id / per, e = id - r * per;
+    b = sequence_of_rank(r, ordered, n, Hq, Hkv, sel_count, seq_n, own_n);
+    split = e / Hkv;
+    hk = e - split * Hkv;
+    bh = b * Hkv + hk;
+  }
   const int row0 = b * Hq + hk * G;
   const int wave = threadIdx.x / kWave, lane = lane_id();
   const int x = lane & 15, j = lane >> 4;
   const bool window = split >= idx_splits;
+  // What does not depend on the sequence's lengths is requested first: this
+  // thread's 8 query dimensions, the selection words and counts.
+  static_assert(G * (D / 8) <= kDThreads, "one piece of the queries per thread");
+  const bool stages = int(threadIdx.x) < G * (D / 8);
+  const int qh = threadIdx.x / (D / 8), qch = threadIdx.x % (D / 8);
+  f32x4 qa = {0.f, 0.f, 0.f, 0.f}, qb = qa;
+  if (stages) {
+    const f32x4* qp = reinterpret_cast<const f32x4*>(q + int64_t(row0 + qh) * D + 8 * qch);
+    qa = qp[0];
+    qb = qp[1];
+  }
+  MaskWords<G> mword{};
+  if (SPARSE && !window)
+    mword = load_mask_words<G>(sel_mask, mask_words, row0, split * chunk, min(n, (split + 1) * chunk));
+  HeadCounts<G> hcount{};   // (loaded in every sparse block, used by the search only: no branch, no early wait)
+  if constexpr (SPARSE) hcount = load_head_counts<G>(sel_count, row0);
   // this sequence's indexed and window rows (the call's n and w unless ragged)
-  const int nb = RAGGED ? min(max(seq_n[b], 0), n) : n;
+  int nb = n;
+  if constexpr (RAGGED) nb = SPARSE && ordered ? __builtin_amdgcn_readlane(own_n, b) : min(max(seq_n[b], 0), n);
   const int wb = RAGGED && seq_w ? min(max(seq_w[b], 0), w) : w;
   const int64_t wbase = RAGGED ? nb : 0;   // first window row in K_loc / V_loc of this sequence
   // indexed rows [c0, c1), then nwin folded window rows from row wrow0 (same buffer)
@@ -684,32 +739,26 @@ __global__ __launch_bounds__(kDThreads) void decode_mfma_kernel(
   const uint32_t region = uint32_t(window ? wb : nb + (fold_wq > 0 ? wb : 0)) * uint32_t(D * 2);   // < 2^31
   const __amdgpu_buffer_rsrc_t Kr = make_rsrc(Kb, region);
   const __amdgpu_buffer_rsrc_t Vr = make_rsrc(Vb, region);
-  constexpr bool kPreMask = kPackedQ;   // (for larger groups the early load costs registers)
-  MaskWords<G> mword{};
-  if (kPreMask && SPARSE && !window) mword = load_mask_words<G>(sel_mask, mask_words, row0, c0, c1);
-  HeadCounts<G> hcount{};   // (loaded in every sparse block, used by the search only: no branch, no early wait)
-  if constexpr (SPARSE) hcount = load_head_counts<G>(sel_count, row0);
 
   // query operands, lane (column c, quarter jj) of k-block kb = dims 32 kb + 8 jj .. +8.
   // G <= 4: one operand per k-block, column c = part * G + head; otherwise one
   // operand per (k-block, part), column c = head. (Columns without a head stay
   // unwritten: each column of the product depends on its own column only, and
   // those are masked.) A thread forms the three parts of 8 dimensions of a head.
-  for (int e = threadIdx.x; e < G * (D / 8); e += kDThreads) {
-    const int h = e / (D / 8), ch = e % (D / 8);
-    const f32x4* qp = reinterpret_cast<const f32x4*>(q + int64_t(row0 + h) * D + 8 * ch);
-    const f32x8 qv = __builtin_shufflevector(qp[0], qp[1], 0, 1, 2, 3, 4, 5, 6, 7) * scale_log2e;
+  if (stages) {
+    const f32x8 qv = __builtin_shufflevector(qa, qb, 0, 1, 2, 3, 4, 5, 6, 7) * scale_log2e;
     bf16x8 parts[kQParts];
     split3(qv, parts);
 #pragma unroll
     for (int t = 0; t < kQParts; ++t)
-      qB[ch / 4][kPackedQ ? 0 : t][16 * (ch % 4) + (kPackedQ ? t * G + h : h)] = __builtin_bit_cast(u32x4, parts[t]);
+      qB[qch / 4][kPackedQ ? 0 : t][16 * (qch % 4) + (kPackedQ ? t * G + qh : qh)] =
+          __builtin_bit_cast(u32x4, parts[t]);
   }
 
   int U;
   if (SPARSE && !window) {
-    U = build_union_list<G, kDThreads, kPreMask>(sel_idx, sel_mask, mask_words, row0, n, c0, c1, nwin, wrow0 - c1, bm, lst, hmask, rng_lo, rng_hi,
-                                       mword, hcount);
+    U = build_union_list<G, kDThreads, true>(sel_idx, sel_mask, mask_words, row0, n, c0, c1, nwin, wrow0 - c1, bm, lst,
+                                             hmask, rng_lo, rng_hi, mword, hcount);
   } else {
     U = (c1 - c0) + nwin;
     if constexpr (SPARSE) {   // window rows of their own: every head takes all of them
@@ -944,14 +993,14 @@ rbq_status launch_g(int G, dim3 grid, hipStream_t stream, const float* q, const 
                     int n, const int32_t* sel_idx, const int32_t* sel_count, const unsigned long long* sel_mask,
                     int mask_words, const void* K_loc, const void* V_loc, int64_t loc_ld, int w, int chunk,
                     int idx_splits, int total, int fold_s0, int fold_wq, float scale_log2e, float* part, int Hq,
-                    int Hkv, const int32_t* seq_n, const int32_t* seq_w) {
+                    int Hkv, const int32_t* seq_n, const int32_t* seq_w, int ordered) {
 #define RBQ_DECODE_CASE(GG)                                                                                       \
   case GG:                                                                                                        \
     if constexpr (DT == RBQ_BF16)                                                                                 \
       decode_mfma_kernel<SPARSE, GG, RAGGED, D><<<grid, kDThreads, 0, stream>>>(                                  \
           q, static_cast<const uint16_t*>(K), static_cast<const uint16_t*>(V), cap, n, sel_idx, sel_count,        \
           sel_mask, mask_words, static_cast<const uint16_t*>(K_loc), static_cast<const uint16_t*>(V_loc), loc_ld, \
-          w, chunk, idx_splits, total, fold_s0, fold_wq, scale_log2e, part, Hq, Hkv, seq_n, seq_w);               \
+          w, chunk, idx_splits, total, fold_s0, fold_wq, scale_log2e, part, Hq, Hkv, seq_n, seq_w, ordered);      \
     else                                                                                                          \
       decode_vec_kernel<DT, SPARSE, GG, RAGGED, D><<<grid, kDThreads, 0, stream>>>(                               \
           q, K, V, cap, n, sel_idx, sel_count, sel_mask, mask_words, K_loc, V_loc, loc_ld, w, chunk, idx_splits,  \
@@ -997,18 +1046,20 @@ rbq_status launch_decode(int32_t batch, int32_t heads_q, int32_t heads_kv, const
   const DecodeSplits sp = decode_splits(batch, heads_kv, n, w, tail, sparse, seq_n != nullptr);
   const dim3 grid = seq_n ? dim3(batch * heads_kv, sp.total()) : dim3(sp.total(), batch * heads_kv);
   float* part = static_cast<float*>(ws);
+  const int64_t blocks = int64_t(grid.x) * grid.y;
+  const int ordered = sparse && seq_n && batch > 1 && batch <= kWave && blocks > kOrderMinBlocks ? batch : 0;
   const float scale_log2e = float(double(sm_scale) * 1.4426950408889634);
   rbq_status st;
 #define RBQ_DECODE_LAUNCH(DT, SP, RG)                                                                              \
   launch_g<DT, SP, RG>(G, grid, stream, q, K, V, cap, n, sel_idx, sel_count, sel_mask, mask_words, K_loc, V_loc, loc_ld, \
                    w, sp.chunk, sp.idx_splits, sp.total(), sp.fold_s0, sp.fold_wq, scale_log2e, part, heads_q,      \
-                   heads_kv, seq_n, seq_w)
+                   heads_kv, seq_n, seq_w, ordered)
   const bool rg = seq_n != nullptr;
   if (D == 64) {   // bf16 on the matrix cores, fp32 on the vector kernel
 #define RBQ_DECODE_LAUNCH64(DT, SP, RG)                                                                             \
   launch_g<DT, SP, RG, 64>(G, grid, stream, q, K, V, cap, n, sel_idx, sel_count, sel_mask, mask_words, K_loc, V_loc, \
                            loc_ld, w, sp.chunk, sp.idx_splits, sp.total(), sp.fold_s0, sp.fold_wq, scale_log2e, part,  \
-                           heads_q, heads_kv, seq_n, seq_w)
+                           heads_q, heads_kv, seq_n, seq_w, ordered)
     if (kv_dtype == RBQ_BF16) {
       if (rg)
         st = sparse ? RBQ_DECODE_LAUNCH64(RBQ_BF16, true, true) : RBQ_DECODE_LAUNCH64(RBQ_BF16, false, true);

@@ -54,3 +54,41 @@ def test_unlisted_rows_stay_out(G, D, n, w, tail, every):
         # probabilities as two bf16 parts (2^-17 of each), logits and sums in fp32 (some 1e-6)
         assert (out[0, h].double() - ref).abs().max() <= 3e-5 * v.abs().max()
         assert abs(float(lse[0, h]) - float(torch.logsumexp(lg, 0))) <= 1e-5 * max(1.0, float(lg.abs().max()))
+
+
+@pytest.mark.parametrize("B,Hkv,D,w", [(40, 8, 64, 0), (64, 4, 128, 9), (65, 4, 128, 9), (2, 3, 64, 30)])
+def test_ragged_batches_in_any_order(B, Hkv, D, w):
+    """Launches of more blocks than are resident at once take the densest sequences first (up to 64 sequences; 65 and
+    the small batch keep their order): every sequence still gets its own rows, also empty ones and equal densities."""
+    G, n, tau = 2, 1100, 1.0 / math.sqrt(D)
+    Hq, cap = Hkv * G, n + w
+    g = torch.Generator(device="cuda").manual_seed(B)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    q, K, V = r(B, Hq, D), r(B, Hkv, cap, D).to(torch.bfloat16), r(B, Hkv, cap, D).to(torch.bfloat16)
+    seq_n = torch.tensor([(0, n, 1, 257, 1024, 700, 700)[b % 7] for b in range(B)], dtype=torch.int32, device="cuda")
+    seq_w = torch.tensor([b % (w + 1) for b in range(B)], dtype=torch.int32, device="cuda")
+    idx = torch.zeros(B, Hq, n, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros(B, Hq, dtype=torch.int32, device="cuda")
+    lists = {}
+    for b in range(B):
+        for h in range(Hq):
+            rows = torch.arange(0, int(seq_n[b]), 1 + (b * 5 + h) % 9, device="cuda")
+            lists[b, h] = rows
+            idx[b, h, :len(rows)] = rows.to(torch.int32)
+            cnt[b, h] = len(rows)
+    out, lse = torch.empty(B, Hq, D, device="cuda"), torch.empty(B, Hq, device="cuda")
+    ws = rbq.workspace(rbq.RBQ_OP_SPARSE_DECODE, B, Hq, Hkv, D, n, w)
+    rbq.rbq_sparse_decode_varlen(B, Hq, Hkv, D, q, K, V, cap, n, w, seq_n, seq_w, idx, cnt, tau, out, lse, ws)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(Hq):
+            nb, wb = int(seq_n[b]), int(seq_w[b])
+            rows = torch.cat([lists[b, h], torch.arange(nb, nb + wb, device="cuda")])
+            if len(rows) == 0:
+                assert float(lse[b, h]) == -math.inf and (out[b, h] == 0).all()
+                continue
+            k, v = K[b, h // G, rows].double(), V[b, h // G, rows].double()
+            lg = k @ q[b, h].double() * tau
+            # (as above)
+            assert (out[b, h].double() - torch.softmax(lg, 0) @ v).abs().max() <= 3e-5 * v.abs().max()
+            assert abs(float(lse[b, h]) - float(torch.logsumexp(lg, 0))) <= 1e-5 * max(1.0, float(lg.abs().max()))
