@@ -2,7 +2,7 @@
 // (Algorithm 2 step 1; Section 3.3 "Query Quantization"; Appendix A.3.2).
 //
 // One block per query head; 2 x 128 threads share the 128 x 128 product (all
-// loads of a thread in flight at once), then 128 threads, one per dimension:
+// loads of a thread in flight at once), then one wave, two dimensions per lane:
 //   y = q - c_q, A = ||y||, u = y / A, q'[j] = sum_d P[d][j] u[d]   (q' = P^T u)
 //   q_l = min q', q_r = max q', Delta = (q_r - q_l) / L,
 //   q_u = clamp(floor((q' - q_l) / Delta + 1/2), 0, L)
@@ -12,7 +12,10 @@
 // separately (no contraction; IEEE division), so the oracle can repeat the
 // decision exactly from the same q'. Bit-plane j of the codes is one wave
 // ballot per 64 dimensions. The cost is one 128 x 128 matrix-vector product
-// per head, amortised over all keys (Section 3.1).
+// per head, amortised over all keys (Section 3.1). A launch of few blocks is bound
+// by its chain of steps: three barriers, wave reductions on the DPP paths and an
+// epilogue within one wave (32 heads: 4.5 us; with twelve barriers and
+// reductions through LDS permutes 5.1).
 #include "encode_dev.h"
 #include "rbq_device.h"
 #include "rbq_internal.h"
@@ -21,68 +24,11 @@ namespace rbq {
 namespace {
 
 constexpr int kQAll = 256;            // threads per block
-// For head dimension D: one thread per output dimension in the epilogue (the
-// first D threads, the lead group), and the matrix-vector product split over
-// kQAll / D thread groups (2 at D = 128, 4 at D = 64).
+// The matrix-vector product is split over kQAll / D thread groups (2 at D = 128, 4 at D = 64).
 template <int D>
 struct QShape {
-  static constexpr int kQWaves = D / kWave;      // waves of the lead group
   static constexpr int kQParts = kQAll / D;
 };
-constexpr int kQWavesMax = kHeadDim / kWave;
-
-// reductions over the first kQWaves waves (the other waves take part in the barriers only)
-template <int kQWaves>
-__device__ __forceinline__ float block_sum(float v, float* red) {
-  v = wave_sum(v);
-  const int w = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane_id() == 0 && w < kQWaves) red[w] = v;
-  __syncthreads();
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < kQWaves; ++i) s += red[i];
-  return s;
-}
-
-// sum over all kQAll threads of the block
-__device__ __forceinline__ float block_sum_all(float v, float* red) {
-  v = wave_sum(v);
-  const int w = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane_id() == 0) red[w] = v;
-  __syncthreads();
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < kQAll / kWave; ++i) s += red[i];
-  return s;
-}
-
-template <int kQWaves>
-__device__ __forceinline__ float block_min(float v, float* red) {
-  v = wave_min(v);
-  const int w = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane_id() == 0 && w < kQWaves) red[w] = v;
-  __syncthreads();
-  float s = red[0];
-#pragma unroll
-  for (int i = 1; i < kQWaves; ++i) s = fminf(s, red[i]);
-  return s;
-}
-
-template <int kQWaves>
-__device__ __forceinline__ float block_max(float v, float* red) {
-  v = wave_max(v);
-  const int w = threadIdx.x / kWave;
-  __syncthreads();
-  if (lane_id() == 0 && w < kQWaves) red[w] = v;
-  __syncthreads();
-  float s = red[0];
-#pragma unroll
-  for (int i = 1; i < kQWaves; ++i) s = fmaxf(s, red[i]);
-  return s;
-}
 
 // The code of one rotated component, every operation rounded on its own.
 __device__ __forceinline__ int quant_code(float x, float ql, float delta, float top) {
@@ -110,7 +56,7 @@ struct QuantArgs {
 // query head `row` (= b * Hq + h), by the kQAll threads of the calling block
 template <int D>
 __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
-  constexpr int kQWaves = QShape<D>::kQWaves, kQParts = QShape<D>::kQParts;
+  constexpr int kQParts = QShape<D>::kQParts;
   constexpr int W = D / 32;                    // words per bit-plane
   const float* __restrict__ q = qa.q;
   const float* __restrict__ P = qa.P;
@@ -122,7 +68,7 @@ __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
   const int Hq = qa.Hq, Hkv = qa.Hkv;
   __shared__ float u_s[D];
   __shared__ float part_s[kQParts][D];
-  __shared__ float red[2 * (kQAll / kWave) + 2 * kQWavesMax];
+  __shared__ f32x2 red[kQAll / kWave];
   const int b = row / Hq;
   const int h = row - b * Hq;
   const int grp = b * Hkv + h / (Hq / Hkv);    // (b, kv head)
@@ -142,9 +88,17 @@ __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
     ck = c_k[int64_t(grp) * D + j];
     y = qj - cq;
   }
-  // the first two waves hold the vector; the block sums include zeros from the others
-  const float A = sqrtf(block_sum_all(y * y, red));
-  const float B0 = block_sum_all(qj * ck, red + kQAll / kWave);
+  // the first D threads hold the vector; the block's sums include zeros from the others
+  const float yy = wave_dot(y, y), qc = wave_dot(qj, ck);
+  if (lane_id() == 0) red[threadIdx.x / kWave] = f32x2{yy, qc};
+  __syncthreads();
+  float A = 0.f, B0 = 0.f;
+#pragma unroll
+  for (int i = 0; i < kQAll / kWave; ++i) {
+    A += red[i].x;
+    B0 += red[i].y;
+  }
+  A = sqrtf(A);
   if (part == 0) u_s[j] = A > 0.f ? y / A : 0.f;
   __syncthreads();
 
@@ -154,44 +108,49 @@ __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
   for (int k = 0; k < kRows; ++k) acc = fmaf(pv[k], u_s[part * kRows + k], acc);
   part_s[part][j] = acc;
   __syncthreads();
-  // every thread computes the sum (in a fixed order); only the lead group uses it
-  acc = part_s[0][j];
-#pragma unroll
-  for (int t = 1; t < kQParts; ++t) acc += part_s[t][j];
-  const bool lead = part == 0;
-  if (qrot_out && lead) qrot_out[int64_t(row) * D + j] = acc;
+  if (threadIdx.x >= kWave) return;
 
-  const float ql = block_min<kQWaves>(acc, red + 2 * (kQAll / kWave));
-  const float qr = block_max<kQWaves>(acc, red + 2 * (kQAll / kWave) + kQWavesMax);
+  // The rest is one wave's, D / 64 dimensions per lane: no more barriers.
+  constexpr int T = D / kWave;
+  const int lane = lane_id();
+  float r[T], ql, qr;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {   // (the groups' shares in a fixed order)
+    r[t] = part_s[0][t * kWave + lane];
+#pragma unroll
+    for (int p = 1; p < kQParts; ++p) r[t] += part_s[p][t * kWave + lane];
+    if (qrot_out) qrot_out[int64_t(row) * D + t * kWave + lane] = r[t];
+    ql = t ? fminf(ql, r[t]) : r[t];
+    qr = t ? fmaxf(qr, r[t]) : r[t];
+  }
+  ql = wave_min(ql);
+  qr = wave_max(qr);
   float delta;
   {
 #pragma clang fp contract(off)
     delta = __fdiv_rn(__fsub_rn(qr, ql), float(qa.levels));
   }
-  const int code = quant_code(acc, ql, delta, float(qa.levels));
-  const float su = block_sum<kQWaves>(float(code), red);   // exact: integers below 2^24
+  int code[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) code[t] = quant_code(r[t], ql, delta, float(qa.levels));
 
-  // bit-plane m, 64 dimensions per wave: low 32 lanes -> word 2w, high -> 2w + 1
-  const int w = j / kWave;
+  // bit-plane m, dimensions 64 t .. + 64: the ballot's low half is word 2 t, its high half word 2 t + 1
   uint32_t* planes = qplanes + int64_t(row) * qa.planes * W;
+  int su = 0;
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     if (m >= qa.planes) break;
-    const uint64_t bal = __ballot((code >> m) & 1);
-    if (lead && lane_id() == 0) {
-      planes[m * W + 2 * w] = uint32_t(bal);
-      planes[m * W + 2 * w + 1] = uint32_t(bal >> 32);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const uint64_t bal = __ballot((code[t] >> m) & 1);
+      su += int(__popcll(bal)) << m;
+      if (lane == 0) *reinterpret_cast<u32x2*>(planes + m * W + 2 * t) = u32x2{uint32_t(bal), uint32_t(bal >> 32)};
     }
   }
-  if (lead && j < RBQ_QSCAL_STRIDE) {
-    float v = 0.f;
-    if (j == 0) v = ql;
-    else if (j == 1) v = delta;
-    else if (j == 2) v = su;
-    else if (j == 3) v = A;
-    else if (j == 4) v = B0;
-    else if (j == 5) v = qr;
-    qscal[int64_t(row) * RBQ_QSCAL_STRIDE + j] = v;
+  if (lane < RBQ_QSCAL_STRIDE) {
+    const float v = lane == 0 ? ql : lane == 1 ? delta : lane == 2 ? float(su) : lane == 3 ? A : lane == 4 ? B0
+                                                                   : lane == 5 ? qr : 0.f;
+    qscal[int64_t(row) * RBQ_QSCAL_STRIDE + lane] = v;
   }
 }
 

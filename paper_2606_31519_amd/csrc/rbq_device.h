@@ -18,20 +18,34 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// v and its value in lane l ^ 32, l ^ 16, l ^ 8, l ^ 4, l ^ 2, l ^ 1 in turn, combined
+// by op (commutative): swaps of half waves and of rows, then DPP. (The rotation by 4
+// stands for l ^ 4: after the step before, lanes l and l ^ 8 agree.)
+#define RBQ_DPP(v, ctrl) \
+  __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (v)), (ctrl), 0xF, 0xF, false))
+template <class Op>
+__device__ __forceinline__ float half_reduce(float v, Op op) {   // (from l ^ 16 on: each half of the wave by itself)
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  v = op(v, RBQ_DPP(v, 0x128));   // row_ror:8
+  v = op(v, RBQ_DPP(v, 0x124));   // row_ror:4
+  v = op(v, RBQ_DPP(v, 0x4E));    // quad_perm [2,3,0,1]
+  return op(v, RBQ_DPP(v, 0xB1));   // quad_perm [1,0,3,2]
+}
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return half_reduce(op(__uint_as_float(a[0]), __uint_as_float(a[1])), op);
+}
+// sum of x * y, the first pair of products in one fma (lane 0's result; lanes of the two halves differ in that rounding)
+__device__ __forceinline__ float wave_dot(float x, float y) {
+  return half_reduce(fmaf(x, y, __shfl_xor(x * y, 32, kWave)), [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float wave_min(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fminf(a, b); });
 }
 __device__ __forceinline__ int wave_sum_int(int v) {
 #pragma unroll
@@ -41,8 +55,6 @@ __device__ __forceinline__ int wave_sum_int(int v) {
 
 // Reductions over each group of 32 lanes (both halves of the wave reduce
 // independently): DPP within 16-lane rows, then a swizzle across row pairs.
-#define RBQ_DPP(v, ctrl) \
-  __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (v)), (ctrl), 0xF, 0xF, false))
 __device__ __forceinline__ float swap16(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));
 }
