@@ -115,9 +115,17 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
+    """The handle of `stream`, or of the current device's current stream: as a
+    plain integer where torch gives one (0.5 us a call; through a Stream object,
+    which the call would only take the handle from, 2.8 us, as long as a launch)."""
     if stream is not None:
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
