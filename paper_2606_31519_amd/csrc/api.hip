@@ -40,14 +40,19 @@ rbq_status decode_step(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t
     return s;
 
   const int64_t rows = int64_t(batch) * heads_q;
-  if (do_flush)
-    s = launch_quantize_flush(batch, heads_q, heads_kv, q, P, c_q, c_k, qplanes, qscal, K_loc, kv_dtype, cap, w, n,
-                              cap, codes, kfac, stream, nullptr, nullptr, 0, kfac16, head_dim);
-  else
-    s = launch_quantize(batch, heads_q, heads_kv, q, P, c_q, c_k, qplanes, qscal, nullptr, stream, 4, head_dim);
-  if (s != RBQ_OK) return s;
-  s = launch_score(batch, heads_q, heads_kv, n, cap, codes, kfac, qplanes, qscal, scores, nullptr, nullptr, stream,
-                   nullptr, kfac16, 4, head_dim);
+  if (!do_flush && quantize_score_fused(batch, heads_q, heads_kv, n, head_dim)) {
+    s = launch_quantize_score(batch, heads_q, heads_kv, n, cap, q, P, c_q, c_k, qplanes, qscal, codes, kfac, kfac16,
+                              scores, stream, head_dim);
+  } else {
+    if (do_flush)
+      s = launch_quantize_flush(batch, heads_q, heads_kv, q, P, c_q, c_k, qplanes, qscal, K_loc, kv_dtype, cap, w, n,
+                                cap, codes, kfac, stream, nullptr, nullptr, 0, kfac16, head_dim);
+    else
+      s = launch_quantize(batch, heads_q, heads_kv, q, P, c_q, c_k, qplanes, qscal, nullptr, stream, 4, head_dim);
+    if (s != RBQ_OK) return s;
+    s = launch_score(batch, heads_q, heads_kv, n, cap, codes, kfac, qplanes, qscal, scores, nullptr, nullptr, stream,
+                     nullptr, kfac16, 4, head_dim);
+  }
   if (s != RBQ_OK) return s;
   s = launch_topp(int32_t(rows), n, scores, p, sm_scale, sel_idx, sel_count, sw.topp, stream, sw.masks);
   if (s != RBQ_OK) return s;

@@ -188,7 +188,7 @@ __device__ __forceinline__ float sum_halves(float x) { return x + __shfl_xor(x, 
 
 template <int DT, bool ROT, int D>
 __global__ __launch_bounds__(long_waves(DT) * kWave) void encode_long_kernel(EncodeArgs ea, int blocks_per_head) {
-  constexpr int kLongWaves = long_waves(DT), kLongThreads = kLongWaves * kWave;
+  constexpr int kLongWaves = long_waves(DT);
   constexpr int W = D / 32;         // code words per key, 32-row blocks of P^T
   constexpr int S = D / 16;         // steps of 16 dimensions
   constexpr int kElem = DT == RBQ_BF16 ? 2 : 4;

@@ -17,54 +17,21 @@
 // epilogue within one wave (32 heads: 4.5 us; with twelve barriers and
 // reductions through LDS permutes 5.1).
 #include "encode_dev.h"
+#include "quantize_dev.h"
 #include "rbq_device.h"
 #include "rbq_internal.h"
 
 namespace rbq {
 namespace {
 
-constexpr int kQAll = 256;            // threads per block
-// The matrix-vector product is split over kQAll / D thread groups (2 at D = 128, 4 at D = 64).
-template <int D>
-struct QShape {
-  static constexpr int kQParts = kQAll / D;
-};
-
-// The code of one rotated component, every operation rounded on its own.
-__device__ __forceinline__ int quant_code(float x, float ql, float delta, float top) {
-#pragma clang fp contract(off)
-  if (!(delta > 0.f)) return 0;
-  const float t = __fdiv_rn(__fsub_rn(x, ql), delta);
-  float r = floorf(__fadd_rn(t, 0.5f));
-  r = fminf(fmaxf(r, 0.f), top);
-  return int(r);
-}
-
-struct QuantArgs {
-  const float* q;
-  const float* P;
-  const float* c_q;      // or NULL
-  const float* c_k;
-  uint32_t* qplanes;
-  float* qscal;
-  float* qrot_out;       // or NULL
-  int Hq, Hkv;
-  int levels;            // 2^B_q - 1
-  int planes;            // bit-planes written per head: 4 (B_q <= 4) or 8
-};
-
 // query head `row` (= b * Hq + h), by the kQAll threads of the calling block
 template <int D>
 __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
   constexpr int kQParts = QShape<D>::kQParts;
-  constexpr int W = D / 32;                    // words per bit-plane
   const float* __restrict__ q = qa.q;
   const float* __restrict__ P = qa.P;
   const float* __restrict__ c_q = qa.c_q;
   const float* __restrict__ c_k = qa.c_k;
-  uint32_t* __restrict__ qplanes = qa.qplanes;
-  float* __restrict__ qscal = qa.qscal;
-  float* __restrict__ qrot_out = qa.qrot_out;
   const int Hq = qa.Hq, Hkv = qa.Hkv;
   __shared__ float u_s[D];
   __shared__ float part_s[kQParts][D];
@@ -110,48 +77,7 @@ __device__ __forceinline__ void quantize_row(const QuantArgs& qa, int row) {
   __syncthreads();
   if (threadIdx.x >= kWave) return;
 
-  // The rest is one wave's, D / 64 dimensions per lane: no more barriers.
-  constexpr int T = D / kWave;
-  const int lane = lane_id();
-  float r[T], ql, qr;
-#pragma unroll
-  for (int t = 0; t < T; ++t) {   // (the groups' shares in a fixed order)
-    r[t] = part_s[0][t * kWave + lane];
-#pragma unroll
-    for (int p = 1; p < kQParts; ++p) r[t] += part_s[p][t * kWave + lane];
-    if (qrot_out) qrot_out[int64_t(row) * D + t * kWave + lane] = r[t];
-    ql = t ? fminf(ql, r[t]) : r[t];
-    qr = t ? fmaxf(qr, r[t]) : r[t];
-  }
-  ql = wave_min(ql);
-  qr = wave_max(qr);
-  float delta;
-  {
-#pragma clang fp contract(off)
-    delta = __fdiv_rn(__fsub_rn(qr, ql), float(qa.levels));
-  }
-  int code[T];
-#pragma unroll
-  for (int t = 0; t < T; ++t) code[t] = quant_code(r[t], ql, delta, float(qa.levels));
-
-  // bit-plane m, dimensions 64 t .. + 64: the ballot's low half is word 2 t, its high half word 2 t + 1
-  uint32_t* planes = qplanes + int64_t(row) * qa.planes * W;
-  int su = 0;
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    if (m >= qa.planes) break;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const uint64_t bal = __ballot((code[t] >> m) & 1);
-      su += int(__popcll(bal)) << m;
-      if (lane == 0) *reinterpret_cast<u32x2*>(planes + m * W + 2 * t) = u32x2{uint32_t(bal), uint32_t(bal >> 32)};
-    }
-  }
-  if (lane < RBQ_QSCAL_STRIDE) {
-    const float v = lane == 0 ? ql : lane == 1 ? delta : lane == 2 ? float(su) : lane == 3 ? A : lane == 4 ? B0
-                                                                   : lane == 5 ? qr : 0.f;
-    qscal[int64_t(row) * RBQ_QSCAL_STRIDE + lane] = v;
-  }
+  quantize_finish<D>(qa, row, part_s, A, B0, true);   // one wave's: no more barriers
 }
 
 template <int D>

@@ -177,6 +177,12 @@ rbq_status launch_encode(int32_t batch, int32_t heads_kv, const void* keys, int3
                          uint32_t* codes, float* kfac, uint32_t flags, float* alpha_out, void* ws,
                          float* rot_out, hipStream_t stream, uint16_t* kfac16 = nullptr,
                          int32_t head_dim = kHeadDim);
+// the fused step's quantisation and scan in one launch (uniform batches, no flush), and whether it applies
+bool quantize_score_fused(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t n, int32_t head_dim);
+rbq_status launch_quantize_score(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t n, int32_t cap,
+                                 const float* q, const float* P, const float* c_q, const float* c_k,
+                                 uint32_t* qplanes, float* qscal, const uint32_t* codes, const float* kfac,
+                                 const uint16_t* kfac16, float* scores, hipStream_t stream, int32_t head_dim);
 // (kfac16: the compact index's fp16 factors, written instead of kfac when non-NULL)
 // bits: B_q, the query's quantisation bits (1..8; 4 bit-planes per head up to 4 bits, 8 above)
 rbq_status launch_quantize(int32_t batch, int32_t heads_q, int32_t heads_kv, const float* q, const float* P,

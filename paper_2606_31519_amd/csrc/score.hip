@@ -32,6 +32,7 @@
 // past it; loads are clamped to the sequence's last key.
 #include <type_traits>
 
+#include "quantize_dev.h"
 #include "rbq_device.h"
 #include "rbq_internal.h"
 
@@ -475,6 +476,140 @@ rbq_status launch_kpt(int kpt, dim3 grid, hipStream_t stream, const uint32_t* co
   return hipGetLastError() == hipSuccess ? RBQ_OK : RBQ_EDEVICE;
 }
 
+// ---------------------------------------------------------------- quantisation and scan in one launch
+// Small launches are bound by launches and by the chain of steps in each: here every
+// block quantises the queries of its KV group itself (the same operations in the same
+// order as quantize_row: bitwise the same codes and scalars), P, the queries and its
+// keys all requested at once, and then scores its keys from LDS. A group's first
+// block writes the planes and scalars out. 32 / 8 heads: 4K keys 8.7 us as two
+// launches, XX; 32K keys 9.6, YY.
+constexpr int kFuseGroup = 4;   // query heads per KV head: one wave finishes one
+static_assert(kScoreThreads == kQAll, "both halves run on blocks of the same size");
+template <int KPT, bool FAC16, int D>
+__global__ __launch_bounds__(kQAll) void quantize_score_kernel(QuantArgs qa, const uint32_t* __restrict__ codes,
+                                                               const f32x2* __restrict__ kfac,
+                                                               const uint16_t* __restrict__ kfac16,
+                                                               float* __restrict__ scores, int n, int cap, int blocks) {
+  constexpr int kQParts = QShape<D>::kQParts, kRows = D / kQParts, T = D / kWave;
+  constexpr int kRound = kQAll / D;                                 // heads per round of the norms
+  constexpr int kRounds = (kFuseGroup + kRound - 1) / kRound;
+  __shared__ float u_s[kFuseGroup][D];
+  __shared__ float part_s[kFuseGroup][kQParts][D];
+  __shared__ f32x2 red[kRounds][kQAll / kWave];
+  __shared__ uint32_t qn_s[kFuseGroup][16];
+  __shared__ float qs_s[kFuseGroup][RBQ_QSCAL_STRIDE];
+  const int G = qa.Hq / qa.Hkv;
+  const int bh = blockIdx.x / blocks, blk = blockIdx.x - bh * blocks;
+  const int b = bh / qa.Hkv, row0 = b * qa.Hq + (bh - b * qa.Hkv) * G;
+  const int j = threadIdx.x % D, part = threadIdx.x / D;           // output dimension, share of the input ones
+  const int wave = threadIdx.x / kWave, lane = lane_id();
+
+  float pv[kRows], qv[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) qv[r] = qa.q[int64_t(row0 + min(r * kRound + part, G - 1)) * D + j];
+  const float cq = qa.c_q ? qa.c_q[int64_t(bh) * D + j] : 0.f, ck = qa.c_k[int64_t(bh) * D + j];
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) pv[k] = qa.P[(part * kRows + k) * D + j];
+  const int i0 = blk * (kScoreThreads * KPT) + threadIdx.x;
+  u32x4 c[KPT];
+  f32x2 fg[KPT];
+  uint16_t fh[KPT];
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    const int64_t i = int64_t(bh) * cap + min(i0 + u * kScoreThreads, n - 1);   // (keys past n are never stored)
+    if (D == 128) {
+      c[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(codes) + i);
+    } else {
+      const u32x2 c2 = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(codes) + i);
+      c[u] = u32x4{c2.x, c2.y, 0u, 0u};
+    }
+    if (FAC16) fh[u] = __builtin_nontemporal_load(kfac16 + i);
+    else fg[u] = __builtin_nontemporal_load(kfac + i);
+  }
+
+  // ||q - c_q|| and <q, c_k>: round r has heads r * kRound + part, T waves each
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const float y = qv[r] - cq;
+    const float yy = wave_dot(y, y), qc = wave_dot(qv[r], ck);
+    if (lane == 0) red[r][wave] = f32x2{yy, qc};
+  }
+  __syncthreads();
+  auto norms = [&](int h, float& A, float& B0) {
+    A = 0.f;
+    B0 = 0.f;
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const f32x2 v = red[h / kRound][h % kRound * T + i];
+      A += v.x;
+      B0 += v.y;
+    }
+    A = sqrtf(A);
+  };
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    const int h = r * kRound + part;
+    float A, B0;
+    norms(h, A, B0);
+    if (h < kFuseGroup) u_s[h][j] = A > 0.f ? (qv[r] - cq) / A : 0.f;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < kFuseGroup; ++h) {
+    if (h >= G) break;   // (uniform)
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) acc = fmaf(pv[k], u_s[h][part * kRows + k], acc);
+    part_s[h][part][j] = acc;
+  }
+  __syncthreads();
+  if (wave < G) {
+    float A, B0;
+    norms(wave, A, B0);
+    const QuantRow<D> o = quantize_finish<D>(qa, row0 + wave, part_s[wave], A, B0, blk == 0);
+    if (lane < RBQ_QSCAL_STRIDE) qs_s[wave][lane] = o.scalar(lane, A, B0);
+    if (lane < 4) {   // word `lane` of the planes in nibble form (D = 64: words 2 and 3 are zero padding)
+      uint32_t a[4], w[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const uint64_t v = lane < 2 ? o.bal[m][0] : T > 1 ? o.bal[m][T - 1] : 0ull;
+        a[m] = lane & 1 ? uint32_t(v >> 32) : uint32_t(v);
+      }
+      planes_to_nibbles(a[0], a[1], a[2], a[3], w);
+      *reinterpret_cast<u32x4*>(&qn_s[wave][4 * lane]) = u32x4{w[0], w[1], w[2], w[3]};
+    }
+  }
+  __syncthreads();
+
+  Spread e[KPT];
+  int pcm[KPT];
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    pcm[u] = 2 * (__popc(c[u].x) + __popc(c[u].y) + __popc(c[u].z) + __popc(c[u].w)) - D;
+    e[u] = spread_code(c[u]);
+  }
+  for (int g = 0; g < G; ++g) {
+    uint32_t qn[16];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(&qn_s[g][4 * t]);
+      qn[4 * t] = v.x; qn[4 * t + 1] = v.y; qn[4 * t + 2] = v.z; qn[4 * t + 3] = v.w;
+    }
+    const float ql = qs_s[g][0], delta = qs_s[g][1], A = qs_s[g][3], B0 = qs_s[g][4];
+    const int su = int(qs_s[g][2]);
+    const float a_delta = A * delta, a_ql = A * ql;
+    float* out = scores + int64_t(row0 + g) * n;
+#pragma unroll
+    for (int u = 0; u < KPT; ++u) {
+      const int i = i0 + u * kScoreThreads;
+      const float y = fmaf(a_delta, float(2 * int(binary_int4_dot(e[u], qn)) - su), a_ql * float(pcm[u]));
+      const float sc = FAC16 ? fmaf(float(__builtin_bit_cast(_Float16, fh[u])), y, B0)
+                             : fmaf(fg[u].x, y, B0 + fg[u].y);
+      if (i < n) put_score(sc, out + i);
+    }
+  }
+}
+
 // the matrix-core form (G = 4 or 8)
 template <bool RAGGED, bool FAC16>
 rbq_status launch_mfma(int kpt, dim3 grid, hipStream_t stream, const uint32_t* codes, const float* kfac,
@@ -544,6 +679,44 @@ rbq_status launch_score(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_
                               heads_q, heads_kv, G, sg, seq_n, planes);
   return launch_score_d<kHeadDim>(kpt, grid, stream, codes, kfac, kfac16, qplanes, qscal, scores, ip_out, pc_out, n,
                                   cap, heads_q, heads_kv, G, sg, seq_n, planes);
+}
+
+// Quantisation and scan in one launch, up to one block of 1024 keys per CU (two at 64
+// dimensions): every block reads P (64 KB, 16 KB at 64 dimensions) and repeats its
+// group's quantisation, which at the last of these sizes already takes what the second
+// launch did (32K keys of 8 heads: 256 blocks). Groups of 8 and 16 heads would repeat
+// two and four times as much. As few keys per lane as keep one block per CU.
+constexpr int64_t kFuseBlocks = 256;
+bool quantize_score_fused(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t n, int32_t head_dim) {
+  if (n <= 0 || heads_q / heads_kv > kFuseGroup) return false;
+  const int64_t blocks = int64_t(batch) * heads_kv * ((int64_t(n) + 4 * kScoreThreads - 1) / (4 * kScoreThreads));
+  return blocks <= (head_dim == 64 ? 2 : 1) * kFuseBlocks;
+}
+
+rbq_status launch_quantize_score(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t n, int32_t cap,
+                                 const float* q, const float* P, const float* c_q, const float* c_k,
+                                 uint32_t* qplanes, float* qscal, const uint32_t* codes, const float* kfac,
+                                 const uint16_t* kfac16, float* scores, hipStream_t stream, int32_t head_dim) {
+  const QuantArgs qa{q, P, c_q, c_k, qplanes, qscal, nullptr, heads_q, heads_kv, 15, 4};
+  const int groups = batch * heads_kv;
+  int kpt = 1;
+  while (kpt < 4 && int64_t(groups) * ((n + kScoreThreads * kpt - 1) / (kScoreThreads * kpt)) > kFuseBlocks) kpt *= 2;
+  const int blocks = (n + kScoreThreads * kpt - 1) / (kScoreThreads * kpt);
+  const f32x2* f2 = reinterpret_cast<const f32x2*>(kfac);
+#define RBQ_FUSED(K, F, DD)                                                                                        \
+  quantize_score_kernel<K, F, DD><<<groups * blocks, kQAll, 0, stream>>>(qa, codes, f2, kfac16, scores, n, cap, blocks)
+#define RBQ_FUSED_K(F, DD)                                                                     \
+  do {                                                                                         \
+    if (kpt == 4) RBQ_FUSED(4, F, DD); else if (kpt == 2) RBQ_FUSED(2, F, DD); else RBQ_FUSED(1, F, DD); \
+  } while (0)
+  if (head_dim == 64) {
+    if (kfac16) RBQ_FUSED_K(true, 64); else RBQ_FUSED_K(false, 64);
+  } else {
+    if (kfac16) RBQ_FUSED_K(true, kHeadDim); else RBQ_FUSED_K(false, kHeadDim);
+  }
+#undef RBQ_FUSED_K
+#undef RBQ_FUSED
+  return hipGetLastError() == hipSuccess ? RBQ_OK : RBQ_EDEVICE;
 }
 
 }  // namespace rbq
