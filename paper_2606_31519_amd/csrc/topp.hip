@@ -3,9 +3,9 @@
 // The selected set is { i : S_i >= s* } where s* is the largest score value
 // whose "mass at or above" reaches p of the softmax total. Instead of a sort
 // (O(n log n)) or Algorithm 3's ternary search over values, s* is found as the
-// boundary key K* of a radix select over the order-preserving 32-bit key of
-// the fp32 score, with bins weighted by softmax mass: levels of 12, 12 and 8
-// key bits.
+// boundary key K* (the order-preserving 32-bit key of its fp32 score): a
+// histogram of softmax masses over bins of the score finds the bin that holds
+// it, and the few keys inside that bin are ranked by their masses.
 //
 // Masses. A key's mass relative to a reference r (a part's maximum, or the
 // row maximum M) is exp2((S - r) * sm_scale * log2(e)) in fp32, as a 2^-40
