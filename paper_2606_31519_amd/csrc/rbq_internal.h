@@ -162,11 +162,6 @@ StepWorkspace step_workspace(void* base, int32_t batch, int32_t heads_q, int32_t
 
 // Encode: centroid partial sums over chunks of kCentroidChunk keys.
 constexpr int kCentroidChunk = 1024;
-// More new keys than this per (b, kv-head) take the long-run kernel, whose blocks
-// first lay out P's parts (about 7 us). No window is longer, so a window encoded by
-// the fused step and by the separate call always takes the same kernel, and so the
-// same rounding.
-constexpr int kEncodeLongMin = RBQ_MAX_WINDOW;
 size_t encode_workspace_bytes(int32_t batch, int32_t heads_kv, int32_t head_dim, int32_t n_new);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
