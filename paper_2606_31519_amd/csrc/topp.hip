@@ -472,15 +472,16 @@ __device__ __forceinline__ u64* part_map(const MapPlan& mp, unsigned char* P2, i
   return mp.own ? reinterpret_cast<u64*>(P2 + kSelP2Cand) + mp.cand_cap : nullptr;
 }
 
-// The products S * c of the keys inside the crossing bin are those in [lo, hi)
-// (from 2^23 on every fp32 value is an integer).
+// The products S * c of the keys inside the crossing bin are those in [lo, hi):
+// fp32 holds halves up to 2^23 in magnitude (the bin of -2^23 has -2^23 + 1/2, too)
+// and integers only, or less, from there on.
 struct BinEdges {
   float lo, hi;
 };
 __device__ __forceinline__ BinEdges bin_edges(int bin) {
   BinEdges e;
   e.lo = float(bin);
-  e.hi = abs(bin) < 8388608 ? e.lo + 1.f : __uint_as_float(__float_as_uint(e.lo) + (bin > 0 ? 1 : -1));
+  e.hi = bin >= -8388608 && bin < 8388608 ? e.lo + 1.f : __uint_as_float(__float_as_uint(e.lo) + (bin > 0 ? 1 : -1));
   return e;
 }
 // Four steps' keys against the crossing bin: lanes K .. K + 3 of `above` and

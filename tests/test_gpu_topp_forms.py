@@ -103,3 +103,15 @@ def test_step_equals_calls(n, w):
         for h in range(8):
             assert np.array_equal(ia[s, h, :cnt[s, h]], ib[s, h, :cnt[s, h]])
     assert torch.equal(a.out, b.out) and torch.equal(a.lse, b.lse)
+
+
+@pytest.mark.parametrize("n", [200, 32768, 32769])
+def test_bins_at_the_end_of_the_fractions(n):
+    """Products S * c of -2^23 + 1/2 and -2^23 share a bin (below -2^23 every fp32 value is an integer): p = 0.3 of 100
+    keys of each is reached within the first."""
+    S = np.full((1, n), -1.1e6, np.float32)
+    S[0, 0:100], S[0, 100:200] = -1027875.0625, -1027875.125
+    c = np.float32(np.float32(float(np.float32(TAU)) * 1.4426950408889634) * np.float32(64.0))
+    assert S[0, 0] * c == np.float32(-8388607.5) and S[0, 100] * c == np.float32(-8388608.0)
+    sel, cnt = _select(S, 0.3, TAU)
+    assert cnt[0] == 100 and np.array_equal(sel[0, :100], np.arange(100))
