@@ -37,13 +37,13 @@
 //            part's keys above that bin in a bitmap and hands its keys inside
 //            the bin (the candidates, with their positions) to the last kernel.
 //            An irregular row (scores that the grid cannot hold, or more
-//            candidates than the buffers take, which the merged masses bound)
-//            gets K* here instead, by an exact three-level select over all of
-//            its keys in every block.
-//   3 final  ranks the row's candidates in LDS (masses relative to M) and so
-//            finds K*, adds the part's candidates >= K* to its bitmap and expands
-//            the bitmap into ascending indices at the offset given by the
-//            selected counts of the parts before it. It reads no scores.
+//            candidates in a part than its buffer takes, which the part's mass
+//            inside the bin bounds) gets K* here instead, by an exact three-level
+//            select over all of its keys in every block: ten times the time.
+//   3 final  ranks the row's candidates (masses relative to M) and so finds K*,
+//            adds the part's candidates >= K* to its bitmap and expands the bitmap
+//            into ascending indices at the offset given by the selected counts of
+//            the parts before it. It reads no scores.
 // Shorter rows: one kernel, one block per row, the scores in registers from the
 // first load to the last store (sel_row_kernel).
 //
@@ -454,7 +454,9 @@ struct P2Head {
 // Where pass 2 leaves the bitmap of a part's keys above the crossing bin: the
 // caller's selection bitmap, which pass 3 completes; without one, the end of the
 // part's candidate room, as long as that leaves half of it (kOwnMapMax
-// sub-chunks); otherwise nowhere, and pass 3 compares the scores with K*.
+// sub-chunks); otherwise nowhere, and pass 3 compares the scores with K*. The room
+// for candidates is the same with and without the caller's bitmap, so that the
+// fused step and the separate call settle the same rows by the exact select.
 constexpr int kMapWords = kSub / kWave;   // words of a sub-chunk
 constexpr int kOwnMapMax = 4;
 struct MapPlan {
@@ -464,8 +466,8 @@ struct MapPlan {
   bool own;          // the part's own bitmap follows its candidates
 };
 inline MapPlan map_plan(u64* masks, int words, int spb) {
-  const bool own = masks == nullptr && spb <= kOwnMapMax;
-  return MapPlan{masks, words, own ? kSelCandCap - kMapWords * spb : kSelCandCap, own};
+  const bool room = spb <= kOwnMapMax;
+  return MapPlan{masks, words, room ? kSelCandCap - kMapWords * spb : kSelCandCap, room && masks == nullptr};
 }
 __device__ __forceinline__ u64* part_map(const MapPlan& mp, unsigned char* P2, int row, int k0) {
   if (mp.masks) return mp.masks + int64_t(row) * mp.words + k0 / kWave;
@@ -660,18 +662,22 @@ __global__ __launch_bounds__(kT, 8) void sel_cand_kernel(const float* __restrict
       }
       need = need1 - (l2 > 0 ? readlane_f64(x2, l2 - 1) : 0.0);
       const int bin = (top - l1) * kSelFine + kSelFine - 1 - l2;
-      // At most how many keys the row has inside the bin: the mass there over
-      // the least mass of one key there (the product S * c is off by up to 2^-24
-      // of itself, the mass by far less than 1e-3 octaves, its truncation by one
-      // unit of the part that shrinks a unit most). Every block of the row comes
-      // to the same answer, so all of them know that the candidates fit.
+      // At most how many keys a part has inside the bin: its mass there over the
+      // least mass of one key there (the product S * c is off by up to 2^-24 of
+      // itself, the mass by far less than 1e-3 octaves, its truncation by one unit
+      // of the part that shrinks a unit most). Every block of the row comes to the
+      // same answer for all parts (lane j: part j), so all of them know that the
+      // candidates fit. (The row's mass against one part's room sent ordinary rows
+      // of a million keys to the exact select: 8 rows of 1048576 normal scores,
+      // sigma 1.5 nats, p = 0.95, 604 us; now 42.)
       const float slack = float(abs(bin)) * 0x1p-22f + 0.1f;
       const float x0 = float(double(bin) - double(M) * double(c)) - slack;
       const float least = __builtin_amdgcn_exp2f(x0 * (1.f / kSelPerOctave)) * kFix - 1.f;
-      const double sum = readlane_f64(x2, kWave - 1) > 0.0 ? readlane_f64(F, l2) : 0.0;
+      const double mass = lane < parts_r ? val_s[lane][kSelFine - 1 - l2] * fac : 0.0;
+      const bool fits = ballot(lane < parts_r && !(mass < double(least) * double(mp.cand_cap))) == 0ull;
       if (lane == 0) {
         bin_s = bin;
-        exact_s = !(sum < double(least) * double(min(kSelCandLds, mp.cand_cap)));
+        exact_s = !fits;
       }
     }
     __syncthreads();
@@ -756,14 +762,15 @@ __global__ __launch_bounds__(kT, 8) void sel_cand_kernel(const float* __restrict
 }
 
 // ---------------------------------------------------------------- ranking the candidates
-// K* among C >= 1 candidate keys in LDS: the largest key whose mass at or above
-// (masses relative to M, need in the same units) reaches need; 0 when none does
-// (every candidate is selected). All kThr threads call it. The candidates fall
+// K* among the candidate keys (at least one): the largest key whose mass at or
+// above (masses relative to M, need in the same units) reaches need; 0 when none
+// does (every candidate is selected). All kThr threads call it; keys(body) calls
+// body(key) for this thread's share of the candidates. The candidates fall
 // into 256 sub-bins of the crossing bin, wave 0 finds the sub-bin where the mass
 // reaches need, and the few keys inside that one are compared in pairs; where it
 // holds more than 64 (ties, or a bin that is one fp32 value) the step repeats on
 // 256 steps of the range of their keys.
-// rank_clear comes before the barrier that publishes ck.
+// rank_clear comes before the barrier that publishes the keys.
 constexpr int kSubBins = 256, kPairMax = kWave;
 struct RankLds {
   u64 h[kSubBins];
@@ -780,9 +787,9 @@ __device__ __forceinline__ void rank_clear(RankLds& L) {
     L.kmax = 0u;
   }
 }
-template <int kThr>
-__device__ __forceinline__ uint32_t rank_candidates(const uint32_t* ck, int C, u64 need, float M, float scale_log2e,
-                                                    float c, int bin, RankLds& L) {
+template <int kThr, class Keys>
+__device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, float M, float scale_log2e, float c,
+                                                    int bin, RankLds& L) {
   const int t = threadIdx.x, lane = lane_id();
   need = need < 1ull ? 1ull : need;
   uint32_t lo = 0u, hi = 0xffffffffu;   // the open keys
@@ -793,13 +800,12 @@ __device__ __forceinline__ uint32_t rank_candidates(const uint32_t* ck, int C, u
       if (shift >= 0) return int((key - lo) >> shift);
       return min(max(int((__fmul_rn(key_score(key), c) - float(bin)) * float(kSubBins)), 0), kSubBins - 1);
     };
-    for (int i = t; i < C; i += kThr) {
-      const uint32_t key = ck[i];
+    keys([&](uint32_t key) {
       if (key >= lo && key <= hi) {
         const u64 e = fixed_mass(key_score(key), M, scale_log2e);
         if (e) atomicAdd(&L.h[slot(key)], e);
       }
-    }
+    });
     __syncthreads();
     if (t < kWave) {
       const u64 b0 = L.h[4 * t], b1 = L.h[4 * t + 1], b2 = L.h[4 * t + 2], b3 = L.h[4 * t + 3];
@@ -818,15 +824,14 @@ __device__ __forceinline__ uint32_t rank_candidates(const uint32_t* ck, int C, u
     if (!L.cr.ok) return 0u;   // block-uniform: no candidate has mass
     const int cs = int(L.cr.bin);
     need = L.cr.need;
-    for (int i = t; i < C; i += kThr) {
-      const uint32_t key = ck[i];
+    keys([&](uint32_t key) {
       if (key >= lo && key <= hi && slot(key) == cs) {
         const uint32_t pos = atomicAdd(&L.cnt, 1u);
         if (pos < uint32_t(kPairMax)) L.rest[pos] = key;
         atomicMin(&L.kmin, key);
         atomicMax(&L.kmax, key);
       }
-    }
+    });
     __syncthreads();
     const int r = int(L.cnt);
     if (r <= kPairMax) {   // block-uniform
@@ -921,40 +926,82 @@ __global__ __launch_bounds__(kFT) void sel_final_kernel(const float* __restrict_
     uint32_t ncand, nabove;
     const uint32_t cb = wave_excl_scan_u32(hd.cand_cnt, &ncand);
     const uint32_t ab = wave_excl_scan_u32(hd.above_cnt, &nabove);
-    const int C = int(ncand);   // (<= kSelCandLds: pass 2 made sure)
+    const int C = int(ncand);
+    // More candidates than the LDS holds (a million keys, or scores within a few
+    // hundredths of a nat): gone through where pass 2 left them, in the L2.
+    const bool held = C <= kSelCandLds;
     const int own0 = __builtin_amdgcn_readlane(int(cb), wk.part);
     own_n = __builtin_amdgcn_readlane(int(hd.cand_cnt), wk.part);
+    auto list = [&](int j) {
+      return reinterpret_cast<const u32x2*>(P2row + int64_t(j) * kSelPart2Bytes + kSelP2Cand);
+    };
     for (int j = wave; j < parts_r; j += kFW) {
       const int c0 = __builtin_amdgcn_readlane(int(cb), j), cn = __builtin_amdgcn_readlane(int(hd.cand_cnt), j);
-      const u32x2* cand = reinterpret_cast<const u32x2*>(P2row + int64_t(j) * kSelPart2Bytes + kSelP2Cand);
-      for (int i = lane; i < cn; i += kWave) {
-        const u32x2 e = j == wave && i == lane ? pre : cand[i];
-        ck[c0 + i] = e.x;
+      if (!held && j != wk.part) continue;   // (wave-uniform)
+      const u32x2* cand = list(j);
+      auto put = [&](int i, u32x2 e) {
+        if (i >= cn) return;
+        if (held) ck[c0 + i] = e.x;
         if (j == wk.part) ci[i] = int32_t(e.y);
+      };
+      int i = lane;
+      if (j == wave) {
+        put(i, pre);
+        i += kWave;
+      }
+      for (; i < cn; i += 4 * kWave) {   // (four loads in flight)
+        if (cn - (i - lane) <= kWave) {  // (wave-uniform)
+          put(i, cand[i]);
+          break;
+        }
+        u32x2 e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = cand[min(i + u * kWave, cn - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) put(i + u * kWave, e[u]);
       }
     }
     __syncthreads();
+    auto before = [&](auto body) {   // body(key, whether it is of a part before this one)
+      if (held) {                    // (block-uniform)
+        for (int i = t; i < C; i += kFT) body(ck[i], i < own0);
+      } else {
+        for (int j = wave; j < parts_r; j += kFW) {
+          const int cn = __builtin_amdgcn_readlane(int(hd.cand_cnt), j);
+          const u32x2* cand = list(j);
+          for (int i = lane; i < cn; i += 4 * kWave) {
+            uint32_t key[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) key[u] = cand[min(i + u * kWave, cn - 1)].x;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (i + u * kWave < cn) body(key[u], j < wk.part);
+          }
+        }
+      }
+    };
+    auto keys = [&](auto body) { before([&](uint32_t key, bool) { body(key); }); };
     kstar = rst.exact ? rst.kstar : 0u;
     if (C > 0) {   // block-uniform
       const float c = scale_log2e * kSelPerOctave;
-      kstar = rank_candidates<kFT>(ck, C, mass_ceil(rst.need), rst.M, scale_log2e, c, rst.bin, rank);
+      kstar = rank_candidates<kFT>(keys, mass_ceil(rst.need), rst.M, scale_log2e, c, rst.bin, rank);
       if (kstar == 0u) {   // (block-uniform) their masses fall short by rounding: all of them are selected
-        for (int i = t; i < C; i += kFT) atomicMin(&rank.kmin, ck[i]);
+        keys([&](uint32_t key) { atomicMin(&rank.kmin, key); });
         __syncthreads();
         kstar = rank.kmin;
       }
       // selected candidates of the parts before this one, and of the row
-      uint32_t nb = 0, ns = 0;   // (of this wave's 64 at a time)
-      for (int i0 = wave * kWave; i0 < C; i0 += kFT) {
-        const int i = i0 + lane;
-        const bool s = i < C && ck[i] >= kstar;
-        ns += uint32_t(__popcll(ballot(s)));
-        nb += uint32_t(__popcll(ballot(s && i < own0)));
-      }
-      if (lane == 0 && ns) atomicAdd(&sel_s, ns);
-      if (lane == 0 && nb) atomicAdd(&before_s, nb);
+      int nb = 0, ns = 0;
+      before([&](uint32_t key, bool b) {
+        ns += key >= kstar ? 1 : 0;
+        nb += key >= kstar && b ? 1 : 0;
+      });
+      ns = wave_sum_i32(ns);
+      nb = wave_sum_i32(nb);
+      if (lane == 0 && ns) atomicAdd(&sel_s, uint32_t(ns));
+      if (lane == 0 && nb) atomicAdd(&before_s, uint32_t(nb));
       for (int i = t; i < own_n; i += kFT)
-        if (ck[own0 + i] < kstar) ci[i] = -1;
+        if ((held ? ck[own0 + i] : list(wk.part)[i].x) < kstar) ci[i] = -1;
       __syncthreads();
     }
     offset = __builtin_amdgcn_readlane(int(ab), wk.part) + int(before_s);
@@ -1147,7 +1194,10 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
       fast = C > 0 && C <= kSelRowCand;
       if (fast) {
         // (the candidates' masses are those the histogram summed, so one of them reaches need_bin)
-        kstar = rank_candidates<kT>(ck, C, need_bin, m, scale_log2e, c, bin, rank);
+        auto held = [&](auto body) {
+          for (int i = t; i < C; i += kT) body(ck[i]);
+        };
+        kstar = rank_candidates<kT>(held, need_bin, m, scale_log2e, c, bin, rank);
         for (; mid; mid &= mid - 1u, ++pos)
           if (ck[pos] >= kstar) word |= mid & (0u - mid);
       }

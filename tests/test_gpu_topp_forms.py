@@ -115,3 +115,19 @@ def test_bins_at_the_end_of_the_fractions(n):
     assert S[0, 0] * c == np.float32(-8388607.5) and S[0, 100] * c == np.float32(-8388608.0)
     sel, cnt = _select(S, 0.3, TAU)
     assert cnt[0] == 100 and np.array_equal(sel[0, :100], np.arange(100))
+
+
+@pytest.mark.parametrize("n,sigma,p", [(1 << 20, 1.5, 0.9), (1 << 20, 2.0, 0.95), (1 << 21, 1.5, 0.9)])
+def test_long_gaussian_rows_are_regular(n, sigma, p):
+    """Thousands of candidates in a row, some tens in each of its parts: no row of these is settled by the exact select
+    of irregular ones (the fifth word of its state, the workspace's last piece), which reads a row 3 times per part."""
+    S = (np.random.default_rng(n).standard_normal((1, n)) * sigma / TAU).astype(np.float32)
+    dS = torch.from_numpy(S).cuda()
+    sel = torch.full((1, n), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = rbq.workspace(rbq.RBQ_OP_TOPP, 1, 1, 1, 128, n)
+    size = rbq.rbq_workspace_bytes(rbq.RBQ_OP_TOPP, 1, 1, 1, 128, n, 0)
+    rbq.rbq_topp_select(1, 1, n, dS, p, TAU, sel, cnt, ws)
+    state = ws[size - 256:size - 256 + 32].cpu().numpy().view(np.uint32)
+    assert state[0] == np.float32(S.max()).view(np.uint32) and state[4] == 0
+    pu.check_topp(S[0], p, TAU, sel[0, :int(cnt[0])].cpu().numpy())
