@@ -51,7 +51,6 @@ constexpr float kSelPerOctave = 64.f;                  // bins per factor of two
 constexpr int kSelCoarse = 64, kSelFine = 64;          // groups of bins, bins per group
 constexpr int kSelCandCap = 2048;                      // candidate keys one part can hand to the final pass
 constexpr int kSelCandLds = 8192;                      // candidate keys of a row the final pass holds in LDS (more: in L2)
-constexpr int kSelRowCand = 4096;                      // the same of a row selected by one block
 constexpr int32_t kToppMaxKeys = int32_t(1) << 24;     // keys per row the fixed-point sums hold
 // per-part records (bytes): the first pass's exact histogram (the part's
 // maximum and total, its 64 group sums and the 64-bin sections of the groups

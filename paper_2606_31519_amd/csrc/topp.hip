@@ -824,12 +824,16 @@ __device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, 
     if (!L.cr.ok) return 0u;   // block-uniform: no candidate has mass
     const int cs = int(L.cr.bin);
     need = L.cr.need;
+    // (counted up to one more than fit, or ties would queue for the counter)
+    uint32_t mn = 0xffffffffu, mx = 0u;
     keys([&](uint32_t key) {
       if (key >= lo && key <= hi && slot(key) == cs) {
-        const uint32_t pos = atomicAdd(&L.cnt, 1u);
-        if (pos < uint32_t(kPairMax)) L.rest[pos] = key;
-        atomicMin(&L.kmin, key);
-        atomicMax(&L.kmax, key);
+        mn = min(mn, key);
+        mx = max(mx, key);
+        if (__hip_atomic_load(&L.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= uint32_t(kPairMax)) {
+          const uint32_t pos = atomicAdd(&L.cnt, 1u);
+          if (pos < uint32_t(kPairMax)) L.rest[pos] = key;
+        }
       }
     });
     __syncthreads();
@@ -847,6 +851,13 @@ __device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, 
       __syncthreads();
       return L.kstar;
     }
+    mn = ~wave_max_u32(~mn);
+    mx = wave_max_u32(mx);
+    if (lane == 0 && mn <= mx) {   // (a wave with a key there)
+      atomicMin(&L.kmin, mn);
+      atomicMax(&L.kmax, mx);
+    }
+    __syncthreads();
     lo = L.kmin;
     hi = L.kmax;
     if (lo == hi) return lo;   // block-uniform: all of them tie
@@ -1082,11 +1093,12 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
                                                      int32_t* __restrict__ sel_count, u64* __restrict__ masks,
                                                      int mask_words, const int32_t* __restrict__ seq_n,
                                                      const float* __restrict__ seq_p, int hq) {
-  // the histogram and the candidate keys; then the selected positions
-  constexpr int kPool = int(sizeof(u64)) * kSelBins + int(sizeof(uint32_t)) * kSelRowCand;
-  __shared__ __attribute__((aligned(16))) unsigned char pool[kPool > PT * kT * 2 ? kPool : PT * kT * 2];
+  // the histogram, then the candidate keys, then the selected positions
+  constexpr int kPool = std::max(int(sizeof(u64)) * kSelBins, PT * kT * int(sizeof(uint16_t)));
+  constexpr int kRowCand = kPool / int(sizeof(uint32_t));   // (all keys of a row of 8192)
+  __shared__ __attribute__((aligned(16))) unsigned char pool[kPool];
   u64* h = reinterpret_cast<u64*>(pool);
-  uint32_t* ck = reinterpret_cast<uint32_t*>(pool + sizeof(u64) * kSelBins);
+  uint32_t* ck = reinterpret_cast<uint32_t*>(pool);
   __shared__ RankLds rank;
   __shared__ u64 wsum[kTW];
   __shared__ Crossing cr;
@@ -1163,7 +1175,8 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
     const u64 total = readlane_u64(upto, kTW - 1);
     u64 need = mass_ceil(double(rs.p) * double(total));
     need = need > total ? total : need;
-    bool fast = g.ok && total > 0ull;   // block-uniform
+    const bool fast = g.ok && total > 0ull;   // block-uniform
+    bool byscore = !fast;                     // K* compared with all scores in the end
     if (fast) {
       const u64 wabove = total - readlane_u64(upto, wave);   // mass of the bins of the waves above
       if (wabove < need && wabove + ws >= need) {            // one wave
@@ -1187,19 +1200,30 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
         pos += uint32_t(__builtin_amdgcn_readfirstlane(int(at)));
         uint32_t q = pos;
         for (uint32_t m2 = mid; m2; m2 &= m2 - 1u, ++q)
-          if (q < uint32_t(kSelRowCand)) ck[q] = score_key(srow[pos0 + __builtin_ctz(m2)]);
+          if (q < uint32_t(kRowCand)) ck[q] = score_key(srow[pos0 + __builtin_ctz(m2)]);
       }
       __syncthreads();
       const int C = int(cand_n);
-      fast = C > 0 && C <= kSelRowCand;
-      if (fast) {
-        // (the candidates' masses are those the histogram summed, so one of them reaches need_bin)
+      // (the candidates' masses are those the histogram summed, so one of them
+      // reaches need_bin; more than the LDS holds are gone through in the registers)
+      byscore = C > kRowCand;
+      if (!byscore) {
         auto held = [&](auto body) {
           for (int i = t; i < C; i += kT) body(ck[i]);
         };
         kstar = rank_candidates<kT>(held, need_bin, m, scale_log2e, c, bin, rank);
         for (; mid; mid &= mid - 1u, ++pos)
           if (ck[pos] >= kstar) word |= mid & (0u - mid);
+      } else if constexpr (PT * kT > kRowCand) {
+        auto own = [&](auto body) {
+          each([&](int k) {   // (lanes past the row: below every bin)
+            float s1 = v[k];
+            asm volatile("" : "+v"(s1));   // (as forget(), for each of the ranking's passes)
+            const float x = __fmul_rn(s1, c);
+            if (x >= be.lo && x < be.hi) body(score_key(s1));
+          });
+        };
+        kstar = rank_candidates<kT>(own, need_bin, m, scale_log2e, c, bin, rank);
       }
     }
     if (!fast) {   // three levels over the row's keys
@@ -1229,6 +1253,8 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
         rest = cr.need;
       }
       kstar = prefix;
+    }
+    if (byscore) {   // block-uniform
       forget();
       const float fstar = key_floor(kstar);   // (NaN for K* = 0: every key, by keys)
       const bool byval = !__builtin_isnan(fstar);

@@ -131,3 +131,15 @@ def test_long_gaussian_rows_are_regular(n, sigma, p):
     state = ws[size - 256:size - 256 + 32].cpu().numpy().view(np.uint32)
     assert state[0] == np.float32(S.max()).view(np.uint32) and state[4] == 0
     pu.check_topp(S[0], p, TAU, sel[0, :int(cnt[0])].cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [4096, 8192, 8193, 12289, 16385, 32768, 32769])
+def test_rows_of_few_scores(n):
+    """All keys in one bin, in as many keys as one block ranks from LDS and in more: one score (every key is selected),
+    and two next to each other (half of the keys hold half of the mass and a little more)."""
+    one = np.full(n, 3.25, np.float32)
+    two = one.copy()
+    two[::2] = np.nextafter(np.float32(3.25), np.float32(4))
+    sel, cnt = _select(np.stack([one, two]), 0.49, TAU)
+    assert cnt[0] == n and np.array_equal(sel[0], np.arange(n))
+    assert cnt[1] == (n + 1) // 2 and np.array_equal(sel[1, :cnt[1]], np.arange(0, n, 2))
