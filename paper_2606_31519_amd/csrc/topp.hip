@@ -9,18 +9,18 @@
 //
 // Masses. A key's mass relative to a reference r (a part's maximum, or the
 // row maximum M) is exp2((S - r) * sm_scale * log2(e)) in fp32, as a 2^-40
-// fixed-point integer; histogram sums are 64-bit integer sums, so they are
-// exact and do not depend on the order of the additions. Parts are combined
-// with the factors exp2((m_j - M) * sm_scale * log2(e)) in fp64 in a fixed
-// order, so the selection is bitwise deterministic. The per-key rounding
-// (< 2^-40 of the part's top mass each) and the fp32 exponential keep the
-// cumulative mass within about 2e-6 of the exact one (fp32 rounding of the
-// exponent's argument dominates for keys far below the maximum).
+// fixed-point integer (2^-48 for rows of 16385 to 32768 keys); histogram sums are
+// 64-bit integer sums, so they are exact and do not depend on the order of the
+// additions. Parts are combined with the factors
+// exp2((m_j - M) * sm_scale * log2(e)) in fp64 in a fixed order, so the selection
+// is bitwise deterministic. The per-key rounding (less than one unit) and the fp32
+// exponential keep the cumulative mass within about 2e-6 of the exact one (fp32
+// rounding of the exponent's argument dominates for keys far below the maximum).
 //
 // First level. A key's bin is the step of its mass on a logarithmic grid:
 // floor(S * sm_scale * log2(e) * 64), 4096 bins of 1/64 octave below the maximum
 // (monotone in S, so every key of a higher bin ranks above every key of a lower
-// one; 63 octaves, past which a key has no mass in 2^-40 units). A bin then holds
+// one; 63 octaves, past which a key has no mass in these units). A bin then holds
 // under 2 % of the keys of an octave: of the 131072 keys of a row about 500 are
 // left to be ranked inside the crossing bin (a bin of the key's top 12 bits held
 // up to 10,000), and the LDS additions spread over hundreds of bins.
@@ -95,12 +95,14 @@ __device__ __forceinline__ int cvt_floor(float x) {
   return r;
 }
 
-// softmax mass of one score in 2^-40 units relative to m (s <= m), truncated;
-// every pass evaluates it with the same instructions, so the same score always
-// gets the same mass. (Whole and fractional part of 2^8 times the mass: every
-// step but the exponential is exact. A NaN gives no mass.)
-__device__ __forceinline__ u64 fixed_mass(float s, float m, float scale_log2e) {
-  const float a = __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(s, m), scale_log2e)) * 256.f;
+// softmax mass of one score in units of 2^-32 / whole relative to m (s <= m),
+// truncated; every pass evaluates it with the same instructions, so the same score
+// always gets the same mass. (Whole and fractional part of `whole` times the mass:
+// every step but the exponential is exact. A NaN gives no mass.)
+constexpr float kWhole = 256.f;         // units of 2^-40: sums of up to 2^24 keys
+constexpr float kWholeFine = 65536.f;   // units of 2^-48: sums of up to 2^16
+__device__ __forceinline__ u64 fixed_mass(float s, float m, float scale_log2e, float whole = kWhole) {
+  const float a = __builtin_amdgcn_exp2f(__fmul_rn(__fsub_rn(s, m), scale_log2e)) * whole;
   const uint32_t lo = cvt_u32(__builtin_amdgcn_fractf(a) * 4294967296.f);
   return (u64(cvt_u32(a)) << 32) | lo;
 }
@@ -351,10 +353,11 @@ __device__ __forceinline__ GridWindow grid_window(float m, float c) {
   return g;
 }
 // One key's mass into the histogram.
-__device__ __forceinline__ void grid_add(u64* h, float s, float m, float scale_log2e, float c, int base) {
+__device__ __forceinline__ void grid_add(u64* h, float s, float m, float scale_log2e, float c, int base,
+                                         float whole = kWhole) {
   // (64-bit integer LDS atomics: under the contention of a few popular bins
   // they run several times faster than fp32 ones)
-  const u64 e = fixed_mass(s, m, scale_log2e);
+  const u64 e = fixed_mass(s, m, scale_log2e, whole);
   const uint32_t d = uint32_t(grid_bin(s, c)) - uint32_t(base);
   if (d < uint32_t(kSelBins)) atomicAdd(&h[d], e);
 }
@@ -789,7 +792,7 @@ __device__ __forceinline__ void rank_clear(RankLds& L) {
 }
 template <int kThr, class Keys>
 __device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, float M, float scale_log2e, float c,
-                                                    int bin, RankLds& L) {
+                                                    int bin, RankLds& L, float whole = kWhole) {
   const int t = threadIdx.x, lane = lane_id();
   need = need < 1ull ? 1ull : need;
   uint32_t lo = 0u, hi = 0xffffffffu;   // the open keys
@@ -802,7 +805,7 @@ __device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, 
     };
     keys([&](uint32_t key) {
       if (key >= lo && key <= hi) {
-        const u64 e = fixed_mass(key_score(key), M, scale_log2e);
+        const u64 e = fixed_mass(key_score(key), M, scale_log2e, whole);
         if (e) atomicAdd(&L.h[slot(key)], e);
       }
     });
@@ -841,7 +844,7 @@ __device__ __forceinline__ uint32_t rank_candidates(const Keys& keys, u64 need, 
     if (r <= kPairMax) {   // block-uniform
       if (t < kWave) {
         const uint32_t key = lane < r ? L.rest[lane] : 0u;
-        const u64 e = lane < r ? fixed_mass(key_score(key), M, scale_log2e) : 0ull;
+        const u64 e = lane < r ? fixed_mass(key_score(key), M, scale_log2e, whole) : 0ull;
         u64 sum = 0;
         for (int i = 0; i < r; ++i)
           sum += uint32_t(__builtin_amdgcn_readlane(int(key), i)) >= key ? readlane_u64(e, i) : 0ull;
@@ -1157,7 +1160,10 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
     __syncthreads();   // (also orders the clearing of h before the adds)
     m = row_max(red[lane & (kTW - 1)]);
     const GridWindow g = grid_window(m, c);
-    each([&](int k) { grid_add(h, v[k], m, scale_log2e, c, g.base); });
+    // A row of more than one sub-chunk has finer units: its masses are not relative
+    // to the maximum of their own sub-chunk, as those of a longer row are.
+    const float whole = nr > kSub ? kWholeFine : kWhole;
+    each([&](int k) { grid_add(h, v[k], m, scale_log2e, c, g.base, whole); });
     forget();
     __syncthreads();
     // the total, the target and the crossing bin: wave w holds bins 256 w ..,
@@ -1211,7 +1217,7 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
         auto held = [&](auto body) {
           for (int i = t; i < C; i += kT) body(ck[i]);
         };
-        kstar = rank_candidates<kT>(held, need_bin, m, scale_log2e, c, bin, rank);
+        kstar = rank_candidates<kT>(held, need_bin, m, scale_log2e, c, bin, rank, whole);
         for (; mid; mid &= mid - 1u, ++pos)
           if (ck[pos] >= kstar) word |= mid & (0u - mid);
       } else if constexpr (PT * kT > kRowCand) {
@@ -1223,7 +1229,7 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
             if (x >= be.lo && x < be.hi) body(score_key(s1));
           });
         };
-        kstar = rank_candidates<kT>(own, need_bin, m, scale_log2e, c, bin, rank);
+        kstar = rank_candidates<kT>(own, need_bin, m, scale_log2e, c, bin, rank, whole);
       }
     }
     if (!fast) {   // three levels over the row's keys
@@ -1242,7 +1248,7 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
           const uint32_t key = score_key(v[k]);
           const bool match = hshift == 32 || (key >> hshift) == prefix;
           if (match) {   // (lanes past the row add no mass)
-            const u64 e = fixed_mass(v[k], m, scale_log2e);
+            const u64 e = fixed_mass(v[k], m, scale_log2e, whole);
             if (e) atomicAdd(&h[(key >> shift) & mask], e);
           }
         });

@@ -143,3 +143,27 @@ def test_rows_of_few_scores(n):
     sel, cnt = _select(np.stack([one, two]), 0.49, TAU)
     assert cnt[0] == n and np.array_equal(sel[0], np.arange(n))
     assert cnt[1] == (n + 1) // 2 and np.array_equal(sel[1, :cnt[1]], np.arange(0, n, 2))
+
+
+def _deep_row(n, first, seed):
+    """One key 37 octaves above keys `first` .. n - 1, which spread over half a nat; no other key counts. p = 1 - 2^-24
+    leaves 2^-24 of the total to be found among them."""
+    S = np.full(n, -1e6, np.float32)
+    S[first:] = -0.5 * np.random.default_rng(seed).random(n - first)
+    S[5] = 37.0 * math.log(2)
+    return S, 1.0 - 2.0 ** -24
+
+
+@pytest.mark.parametrize("n", [16385, 20000, 32768])
+def test_masses_far_below_the_maximum(n):
+    """The keys' masses are 5 to 8 units of 2^-40. Of units of 2^-48 a mass loses less than one: all of them together no
+    more than 16384, which moves the boundary by at most that over the smallest mass, 2^11 e^-1/2 units."""
+    S, p = _deep_row(n, n - 16384 if n > 16385 else 16, 7)
+    sel, cnt = _select(S[None], p, 1.0)
+    m = np.exp(S.astype(np.float64) - float(S[5]))
+    order = np.argsort(-S, kind="stable")
+    want = int(np.searchsorted(np.cumsum(m[order]), p * m.sum())) + 1
+    assert 1000 < want < 16000
+    slack = 16384 / (2.0 ** 11 * math.exp(-0.5)) + 1
+    assert abs(int(cnt[0]) - want) <= slack, (cnt[0], want)
+    assert np.array_equal(sel[0, :cnt[0]], np.sort(order[:cnt[0]]))
