@@ -63,7 +63,11 @@
 // Ragged batches (seq_n / seq_p != NULL): row r of sequence b = r / Hq has
 // seq_n[b] keys (clamped to [0, n]; n stays the row stride and sizes the grid)
 // and its own p = seq_p[b]. Blocks past a row's keys leave at once; rows whose
-// p is >= 1 skip the first two passes, and the last pass selects every key.
+// p is >= 1 skip the first two passes, and the last pass selects every key. Where
+// n calls for three passes, the rows of up to kSelRowMax keys are still selected by
+// one block each, in a launch before them: a row's form, and so the rounding of its
+// sums, depends on its own length only. (us a call, before / with that launch: 16
+// sequences of 4K to 64K keys 71 / 65, of 33K to 63K 74 / 76; 4 of 10K to 48K 23 / 31.)
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -339,7 +343,7 @@ __device__ __forceinline__ float key_floor(uint32_t K) { return key_score(K); }
 __device__ __forceinline__ int grid_bin(float s, float c) { return cvt_floor(__fmul_rn(s, c)); }
 // The window of kSelBins bins below a maximum: `top` is the absolute index of
 // the group of 64 bins that holds it, the window the 64 groups up to it. It
-// reaches 63 octaves down, where a key has no mass left in 2^-40 units (and so
+// reaches 63 octaves down, where a key has no mass left in these units (and so
 // has every key that the window leaves out).
 struct GridWindow {
   int top, base;   // group of the maximum; first bin of the window
@@ -394,7 +398,7 @@ __global__ __launch_bounds__(kT, 8) void sel_hist_kernel(const float* __restrict
   const int parts = tp.parts;
   const RowSel rs = RAGGED ? row_sel(seq_n, seq_p, hq, wk.row, n, 0.5f) : RowSel{n, 0.5f};
   const int k0 = wk.part * spb * kSub;
-  if (k0 >= rs.n || (RAGGED && rs.p >= 1.f)) return;   // block-uniform: no histogram needed here
+  if (k0 >= rs.n || (RAGGED && (rs.n <= kSelRowMax || rs.p >= 1.f))) return;   // block-uniform: no histogram needed
   const int k1 = min(rs.n, k0 + spb * kSub);
   const float* srow = scores + int64_t(wk.row) * n;
   const int t = threadIdx.x;
@@ -579,7 +583,7 @@ __global__ __launch_bounds__(kT, 8) void sel_cand_kernel(const float* __restrict
   const int parts = tp.parts;
   const RowSel rs = RAGGED ? row_sel(seq_n, seq_p, hq, wk.row, n, p) : RowSel{n, p};
   const int k0 = wk.part * spb * kSub;
-  if (k0 >= rs.n || (RAGGED && rs.p >= 1.f)) return;   // block-uniform
+  if (k0 >= rs.n || (RAGGED && (rs.n <= kSelRowMax || rs.p >= 1.f))) return;   // block-uniform
   const int k1 = min(rs.n, k0 + spb * kSub);
   const int parts_r = (rs.n + spb * kSub - 1) / (spb * kSub);   // parts holding keys of this row
   const float* srow = scores + int64_t(wk.row) * n;
@@ -909,10 +913,7 @@ __global__ __launch_bounds__(kFT) void sel_final_kernel(const float* __restrict_
   const int parts = tp.parts;
   const RowSel rs = RAGGED ? row_sel(seq_n, seq_p, hq, wk.row, n, p) : RowSel{n, p};
   const int k0 = wk.part * spb * kSub;
-  if (k0 >= rs.n) {   // block-uniform: no key of this row here (a row without keys selects none)
-    if (RAGGED && rs.n == 0 && wk.part == 0 && threadIdx.x == 0) sel_count[wk.row] = 0;
-    return;
-  }
+  if (k0 >= rs.n || (RAGGED && rs.n <= kSelRowMax)) return;   // block-uniform: no key of this row here
   const int k1 = min(rs.n, k0 + spb * kSub);
   const int span = spb * kSub;
   const int parts_r = (rs.n + span - 1) / span;
@@ -1112,6 +1113,7 @@ __global__ __launch_bounds__(kT) void sel_row_kernel(const float* __restrict__ s
   const RowSel rs = RAGGED ? row_sel(seq_n, seq_p, hq, row, n, p) : RowSel{n, p};
   const int t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int nr = rs.n;
+  if (RAGGED && nr > PT * kT) return;   // block-uniform: a row of the three passes
   if (nr == 0) {   // block-uniform: a row without keys selects none
     if (t == 0) sel_count[row] = 0;
     return;
@@ -1312,6 +1314,21 @@ __global__ __launch_bounds__(kAllThreads) void topp_all_kernel(int n, int32_t* _
   }
 }
 
+// rows of up to `most` keys (n: their stride)
+template <bool RAGGED>
+void sel_rows(int rows, hipStream_t stream, int most, int n, const float* scores, float p, float scale_log2e,
+              int32_t* sel_idx, int32_t* sel_count, u64* masks, int mask_words, const int32_t* seq_n,
+              const float* seq_p, int heads_q) {
+#define RBQ_SEL_ROW(PT)                                                                                            \
+  sel_row_kernel<RAGGED, PT><<<rows, kT, 0, stream>>>(scores, n, p, scale_log2e, sel_idx, sel_count, masks, mask_words, \
+                                                      seq_n, seq_p, heads_q)
+  if (most <= 4 * kT) RBQ_SEL_ROW(4);
+  else if (most <= 8 * kT) RBQ_SEL_ROW(8);
+  else if (most <= 16 * kT) RBQ_SEL_ROW(16);
+  else RBQ_SEL_ROW(32);
+#undef RBQ_SEL_ROW
+}
+
 template <bool RAGGED, bool MULTI>
 void sel_passes(int rows, hipStream_t stream, int n, const ToppPlan& pl, const float* scores, float p,
                 float scale_log2e, const ToppWorkspace& w, int32_t* sel_idx, int32_t* sel_count, u64* masks,
@@ -1325,19 +1342,6 @@ void sel_passes(int rows, hipStream_t stream, int n, const ToppPlan& pl, const f
                                                           w.state, mp, seq_n, seq_p, heads_q);
   sel_final_kernel<RAGGED, MULTI><<<grid, kFT, 0, stream>>>(scores, n, pl.spb, tp, 1, p, scale_log2e, w.part2, w.state,
                                                            sel_idx, sel_count, mp, seq_n, seq_p, heads_q);
-}
-
-template <bool RAGGED>
-void sel_rows(int rows, hipStream_t stream, int n, const float* scores, float p, float scale_log2e, int32_t* sel_idx,
-              int32_t* sel_count, u64* masks, int mask_words, const int32_t* seq_n, const float* seq_p, int heads_q) {
-#define RBQ_SEL_ROW(PT)                                                                                            \
-  sel_row_kernel<RAGGED, PT><<<rows, kT, 0, stream>>>(scores, n, p, scale_log2e, sel_idx, sel_count, masks, mask_words, \
-                                                      seq_n, seq_p, heads_q)
-  if (n <= 4 * kT) RBQ_SEL_ROW(4);
-  else if (n <= 8 * kT) RBQ_SEL_ROW(8);
-  else if (n <= 16 * kT) RBQ_SEL_ROW(16);
-  else RBQ_SEL_ROW(32);
-#undef RBQ_SEL_ROW
 }
 
 }  // namespace
@@ -1357,13 +1361,16 @@ rbq_status launch_topp(int32_t rows, int32_t n, const float* scores, float p, fl
   const float scale_log2e = float(double(sm_scale) * 1.4426950408889634);
   if (n <= kSelRowMax) {
     if (ragged)
-      sel_rows<true>(rows, stream, n, scores, p, scale_log2e, sel_idx, sel_count, masks, mask_words, seq_n, seq_p,
+      sel_rows<true>(rows, stream, n, n, scores, p, scale_log2e, sel_idx, sel_count, masks, mask_words, seq_n, seq_p,
                      heads_q);
     else
-      sel_rows<false>(rows, stream, n, scores, p, scale_log2e, sel_idx, sel_count, masks, mask_words, nullptr, nullptr,
-                      heads_q);
+      sel_rows<false>(rows, stream, n, n, scores, p, scale_log2e, sel_idx, sel_count, masks, mask_words, nullptr,
+                      nullptr, heads_q);
     return hipGetLastError() == hipSuccess ? RBQ_OK : RBQ_EDEVICE;
   }
+  if (seq_n)
+    sel_rows<true>(rows, stream, kSelRowMax, n, scores, p, scale_log2e, sel_idx, sel_count, masks, mask_words, seq_n,
+                   seq_p, heads_q);
   const ToppPlan pl = topp_plan(n);
   const ToppWorkspace w = topp_workspace(ws, rows, n);
 #define RBQ_SEL_PASSES(RG, MU)                                                                               \

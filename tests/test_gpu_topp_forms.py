@@ -167,3 +167,27 @@ def test_masses_far_below_the_maximum(n):
     slack = 16384 / (2.0 ** 11 * math.exp(-0.5)) + 1
     assert abs(int(cnt[0]) - want) <= slack, (cnt[0], want)
     assert np.array_equal(sel[0, :cnt[0]], np.sort(order[:cnt[0]]))
+
+
+def test_a_row_alone_and_in_a_longer_batch():
+    """A sequence of a ragged batch selects the keys that it selects alone, also where the batch's longest row takes the
+    other form and the boundary lies where the units of the masses tell."""
+    n, lens = 40000, [16384, 16385, 20000, 32768, 32769, 40000, 9000]
+    S = np.full((len(lens), n), -math.inf, np.float32)
+    ps = []
+    for i, nr in enumerate(lens):
+        if nr < 16384:
+            S[i, :nr], p = np.random.default_rng(i).standard_normal(nr) * 3, 0.9
+        else:
+            S[i, :nr], p = _deep_row(nr, nr - 15000, i)
+        ps.append(float(np.float32(p)))
+    dS, B = torch.from_numpy(S).cuda(), len(lens)
+    sel = torch.full((B, n), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros(B, dtype=torch.int32, device="cuda")
+    rbq.rbq_topp_select_varlen(B, 1, n, torch.tensor(lens, dtype=torch.int32, device="cuda"), dS,
+                               torch.tensor(ps, device="cuda"), 1.0, sel, cnt,
+                               rbq.workspace(rbq.RBQ_OP_TOPP, B, 1, 1, 128, n))
+    sel, cnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    for i, nr in enumerate(lens):
+        s1, c1 = _select(S[i:i + 1, :nr], ps[i], 1.0)
+        assert cnt[i] == c1[0] and np.array_equal(sel[i, :cnt[i]], s1[0, :c1[0]]), nr
