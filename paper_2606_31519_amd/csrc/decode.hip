@@ -42,7 +42,7 @@
 // (clamped to [0, n]) and seq_w[b] window rows (clamped to [0, w]; all w when
 // seq_w is NULL), the window being its cache tail, rows [seq_n[b], seq_n[b] +
 // seq_w[b]) of K / V (K_loc = K, loc_ld = cap). The grid is sized by n and w
-// and launched split-major (many blocks of the sparse call: the densest
+// and launched split-major (many long blocks of the sparse call: the densest
 // sequences first, see sequence_of_rank); a sequence's window is spread over its own splits,
 // and a split past its rows writes an empty partial state and leaves.
 #include <cmath>
@@ -629,8 +629,15 @@ __device__ __forceinline__ void split3(const f32x8 x, bf16x8* p) {
 // Blocks of dense sequences take several times as long as the others (16 sequences
 // of 2K to 32K keys, p 0.5 to 0.95: 37 to 46 us against 7 to 13), and started last
 // they run on alone: 72 us for that launch, densest first 58. The order costs a block
-// one more round of loads, so launches that are resident at once keep theirs.
-constexpr int kOrderMinBlocks = 1024;   // 4 blocks on each of 256 CUs
+// one more round of loads, so launches that are resident at once keep theirs (64
+// dimensions, 6 x 28K keys, 1344 blocks: 29.9 us, ordered 34.4), and so do launches
+// in the shortest chunks, whose blocks are too short for it (32 / 8 heads of 128, 9 x
+// 4K keys, 1152 blocks: 19.5 us, ordered 22.4; 6 x 8K, 1536 blocks: 21.9 and 22.9).
+// Longer ones gain: 12 x 8K, chunks of 512: 44.5 -> 33.7; 64 dimensions, 8 x 28K:
+// 47.8 -> 36.2; groups of 16, 12 x 32K, 1512 blocks: 73.6 -> 55.6.
+constexpr int kOrderMinChunk = 512;
+// blocks resident at once (256 CUs; registers, for groups of 16 heads the LDS)
+constexpr int64_t resident_blocks(int D, int G) { return 256 * (D == 64 ? (G == 16 ? 4 : 6) : (G == 16 ? 2 : 4)); }
 constexpr int kOrderHeads = 8;
 __device__ __forceinline__ int sequence_of_rank(int r, int batch, int n, int Hq, int Hkv,
                                                 const int32_t* __restrict__ sel_count,
@@ -1047,7 +1054,8 @@ rbq_status launch_decode(int32_t batch, int32_t heads_q, int32_t heads_kv, const
   const dim3 grid = seq_n ? dim3(batch * heads_kv, sp.total()) : dim3(sp.total(), batch * heads_kv);
   float* part = static_cast<float*>(ws);
   const int64_t blocks = int64_t(grid.x) * grid.y;
-  const int ordered = sparse && seq_n && batch > 1 && batch <= kWave && blocks > kOrderMinBlocks ? batch : 0;
+  const int ordered = sparse && seq_n && batch > 1 && batch <= kWave && sp.chunk >= kOrderMinChunk &&
+                              blocks > resident_blocks(D, G) ? batch : 0;
   const float scale_log2e = float(double(sm_scale) * 1.4426950408889634);
   rbq_status st;
 #define RBQ_DECODE_LAUNCH(DT, SP, RG)                                                                              \

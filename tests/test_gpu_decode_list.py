@@ -56,10 +56,12 @@ def test_unlisted_rows_stay_out(G, D, n, w, tail, every):
         assert abs(float(lse[0, h]) - float(torch.logsumexp(lg, 0))) <= 1e-5 * max(1.0, float(lg.abs().max()))
 
 
-@pytest.mark.parametrize("B,Hkv,D,w", [(40, 8, 64, 0), (64, 4, 128, 9), (65, 4, 128, 9), (2, 3, 64, 30)])
+@pytest.mark.parametrize("B,Hkv,D,w", [(40, 8, 64, 0), (64, 4, 128, 9), (65, 4, 128, 9), (2, 3, 64, 30), (64, 9, 128, 9),
+                                       (64, 13, 64, 0), (65, 9, 128, 9)])
 def test_ragged_batches_in_any_order(B, Hkv, D, w):
-    """Launches of more blocks than are resident at once take the densest sequences first (up to 64 sequences; 65 and
-    the small batch keep their order): every sequence still gets its own rows, also empty ones and equal densities."""
+    """Launches of more blocks than are resident at once, in chunks of 512 keys or more, take the densest sequences first
+    (64 sequences x 9 or 13 KV heads here; the others keep their order): every sequence still gets its own rows, also
+    empty ones and equal densities."""
     G, n, tau = 2, 1100, 1.0 / math.sqrt(D)
     Hq, cap = Hkv * G, n + w
     g = torch.Generator(device="cuda").manual_seed(B)
