@@ -42,9 +42,9 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelPerThread = 16;
 constexpr int kSelSub = kSelThreads * kSelPerThread;   // 16384 keys per sub-chunk
 constexpr int kSelMaxParts = 64;                       // parts per row (longer rows take more sub-chunks per part)
-// keys of a row one block holds in registers (32 per thread). One block per row against three passes, in us per call at
-// p = 0.95: 32 rows of 4096 / 16384 / 32768 keys 7.4 / 10.0 / 13.6 against 15.0 / 16.1 / 16.4, 512 rows of 32768 35
-// against 48. Twice the keys would not fit the registers, and at 32 rows one block would fall behind the three passes.
+// keys of a row one block holds in registers (32 per thread). One block per row against three passes, in us per separate
+// call on normal scores of sigma 2 nats, p = 0.95: 32 rows of 4096 / 16384 / 32768 keys 7.4 / 10.0 / 13.6 against 15.0 /
+// 16.1 / 16.4, 512 rows of 32768 35 against 48. Twice the keys would not fit the registers, and at 32 rows one block would fall behind the three passes.
 constexpr int kSelRowMax = 32768;
 constexpr int kSelBins = 4096;                         // bins of a histogram
 constexpr float kSelPerOctave = 64.f;                  // bins per factor of two of the softmax mass

@@ -481,8 +481,10 @@ rbq_status launch_kpt(int kpt, dim3 grid, hipStream_t stream, const uint32_t* co
 // block quantises the queries of its KV group itself (the same operations in the same
 // order as quantize_row: bitwise the same codes and scalars), P, the queries and its
 // keys all requested at once, and then scores its keys from LDS. A group's first
-// block writes the planes and scalars out. 32 / 8 heads: 4K keys 8.7 us as two
-// launches, XX; 32K keys 9.6, YY.
+// block writes the planes and scalars out. A step of 32 / 8 heads at p = 0.8 in
+// a graph, with two launches / with one: 4K keys 27.4 / 25.5 us, 16K 30.5 / 29.5, 32K
+// 36.8 / 35.7; 64 dimensions, 4K 26.9 / 23.7, 64K 41.8 / 38.8; 256 groups of one head,
+// 1K keys each, 40.3 / 24.8.
 constexpr int kFuseGroup = 4;   // query heads per KV head: one wave finishes one
 static_assert(kScoreThreads == kQAll, "both halves run on blocks of the same size");
 template <int KPT, bool FAC16, int D>
@@ -683,9 +685,11 @@ rbq_status launch_score(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_
 
 // Quantisation and scan in one launch, up to one block of 1024 keys per CU (two at 64
 // dimensions): every block reads P (64 KB, 16 KB at 64 dimensions) and repeats its
-// group's quantisation, which at the last of these sizes already takes what the second
-// launch did (32K keys of 8 heads: 256 blocks). Groups of 8 and 16 heads would repeat
-// two and four times as much. As few keys per lane as keep one block per CU.
+// group's quantisation, so what it gains shrinks with the blocks. The lines are a round
+// number of blocks per CU and no break-even: a step with two launches / with one just
+// past them, 64K keys 42.5 / 41.8 us (512 blocks), at 64 dimensions 96K 44.7 / 41.6 (768)
+// and 256K 64.4 / 61.0 (2048). Groups of 8 and 16 heads would repeat two and four times
+// as much (not measured). As few keys per lane as keep one block per CU.
 constexpr int64_t kFuseBlocks = 256;
 bool quantize_score_fused(int32_t batch, int32_t heads_q, int32_t heads_kv, int32_t n, int32_t head_dim) {
   if (n <= 0 || heads_q / heads_kv > kFuseGroup) return false;

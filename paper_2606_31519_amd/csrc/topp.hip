@@ -353,7 +353,7 @@ __device__ __forceinline__ GridWindow grid_window(float m, float c) {
   GridWindow g;
   g.ok = fabsf(__fmul_rn(m, c)) < 1073741824.f;
   g.top = g.ok ? grid_bin(m, c) >> 6 : 0;
-  g.base = g.ok ? (g.top - (kSelCoarse - 1)) * kSelFine : INT_MAX;   // (not ok: no key reaches the window)
+  g.base = g.ok ? (g.top - (kSelCoarse - 1)) * kSelFine : INT_MAX;   // (not ok: the histogram is not used)
   return g;
 }
 // One key's mass into the histogram.

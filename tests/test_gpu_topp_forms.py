@@ -38,7 +38,7 @@ def _rows(n, seed):
         np.where(r.random(n) < 0.3, -np.inf, x / TAU),     # masked keys
         np.where(np.arange(n) % 7 == 0, x / TAU, np.finfo(np.float32).min),   # the same with the lowest value
         -np.abs(x) * 1e-30,                                # around zero
-        tail,                                              # the target may lie below the window
+        tail,                                              # one key 58 octaves above all others
     ])
 
 
@@ -52,16 +52,17 @@ def test_forms_against_the_oracle(n, p):
 
 
 @pytest.mark.parametrize("n", [20000, 40000])
-def test_targets_below_the_window(n):
-    """Half of the mass sits more than 2^31.5 below the top key: p just under 1 has its boundary there. A mass that far
-    down is a 2^-40 integer of about 60 units, truncated: each key is off by up to 1 / 60 of itself."""
+def test_boundary_far_below_the_maximum(n):
+    """The top key alone holds less than p of the mass (0.99999953 at n = 20000, 0.99999907 at 40000), and the keys tied
+    34.5 octaves below it (45 units of 2^-40 each) hold more than the rest of p: exactly these n / 2 keys."""
     S = np.zeros((1, n))
     S[0, 5] = 34.5 * math.log(2) / TAU
     S[0, n // 2:] -= 2.0 / TAU
-    sel, cnt = _select(S, 1.0 - 2e-7, TAU)
-    assert sel[0, 0] >= 0 and 5 in sel[0, :cnt[0]]
-    got = sel[0, :cnt[0]]
-    assert np.array_equal(got, np.sort(got)) and (cnt[0] == 1 or cnt[0] >= n // 2)
+    m = np.exp((S[0] - S[0, 5]) * TAU)
+    p = float(np.float32(1.0 - 2e-7))
+    assert m[5] < p * m.sum() < 0.99 * m[:n // 2].sum() + 0.01 * m[5]
+    sel, cnt = _select(S, p, TAU)
+    assert cnt[0] == n // 2 and np.array_equal(sel[0, :cnt[0]], np.arange(n // 2))
 
 
 @pytest.mark.parametrize("n", [5000, 40000])
