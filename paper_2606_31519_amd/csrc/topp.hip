@@ -562,6 +562,9 @@ __device__ __forceinline__ void select_ballots(const float* v, int base, int end
   }
 }
 
+// (Two blocks per CU need 8 waves per SIMD, for which four scalar registers, and in the
+// ragged form one vector register, are kept in scratch; with those in registers one
+// block fits, and 256 rows of 131072 keys take 97 us for 84.)
 template <bool RAGGED, bool MULTI>
 __global__ __launch_bounds__(kT, 8) void sel_cand_kernel(const float* __restrict__ scores, int n, int spb, TilePlace tp,
                                                       int group, float p, float scale_log2e,
