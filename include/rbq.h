@@ -264,7 +264,9 @@ rbq_status rbq_decode_step(int32_t batch, int32_t heads_q, int32_t heads_kv, int
  *   seq_p [B] float (device): its p. A value >= 1 selects every key; a value
  *         <= 0 or NaN acts as the smallest positive p (the top key and its ties).
  * The results for sequence b are those of the uniform call with B = 1, n =
- * seq_n[b], w = seq_w[b] and p = seq_p[b] (bitwise for scores and selections).
+ * seq_n[b], w = seq_w[b] and p = seq_p[b] (bitwise for scores, and for selections
+ * where n <= 1048576; beyond, a row's masses are summed in parts that grow with n,
+ * and a key at the Top-p boundary may fall either way).
  * Entries of scores and sel_idx past a sequence's count are unspecified. The
  * device counts are not checked on the host: n + w <= cap keeps every row in
  * the cache. Workspaces: as for the uniform op with the same n and w.
