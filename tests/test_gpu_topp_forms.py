@@ -192,3 +192,24 @@ def test_a_row_alone_and_in_a_longer_batch():
     for i, nr in enumerate(lens):
         s1, c1 = _select(S[i:i + 1, :nr], ps[i], 1.0)
         assert cnt[i] == c1[0] and np.array_equal(sel[i, :cnt[i]], s1[0, :c1[0]]), nr
+
+
+@pytest.mark.parametrize("n,spread", [(1 << 19, 0.8), (1 << 20, 1.5)])
+def test_step_equals_calls_on_long_rows(n, spread):
+    """The same where a row has thousands of candidates (normal scores of `spread` nats): step and calls settle it alike,
+    by sums of the same form."""
+    H, D = 2, 64
+    g = torch.Generator(device="cuda").manual_seed(n)
+    K, V = (torch.randn(1, H, n, D, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(1, H, D, device="cuda", generator=g)
+    q *= spread * math.sqrt(D) / q.norm(dim=2, keepdim=True)
+    st = pipeline.DecodeState(1, H, H, D, n, n, 0, K, V, q, torch.from_numpy(gen.haar_rotation(D)).cuda())
+    st.build_index()
+    got = []
+    for step in (st.step_calls, st.step):
+        st.sel_idx.fill_(-1)
+        step(0.9, flush=False)
+        got.append([t.clone() for t in (st.scores, st.sel_count, st.sel_idx, st.out, st.lse)])
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+    assert 0.2 * n < int(got[0][1][0, 0]) < 0.95 * n
